@@ -1,6 +1,5 @@
 // Arguments and fused per-value loads and stores shared by the DFT pass
-// kernels (the three-pass path of kernels_fft.hip and the two-pass 256^3 path
-// of kernels_fft4.hip).
+// kernels (lines, planes and tiles of the general path, and the 256^3 path).
 #pragma once
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -14,17 +13,12 @@ namespace os3d {
 constexpr int kMaxBatch = 64;    // orientation pairs per launch
 
 enum LoadMode { LM_REAL = 0, LM_C = 1, LM_MULBANK = 2, LM_UIN = 3, LM_DIVM = 4 };
-enum StoreMode { SM_C = 0, SM_UOUT = 1, SM_ACCUM = 2, SM_REAL = 3, SM_PHI = 4 };
+enum StoreMode { SM_C = 0, SM_UOUT = 1, SM_ACCUM = 2, SM_REAL = 3 };
 
 struct PassArgs {
-  int axis;  // 0 = z, 1 = y, 2 = x
   int Nz, Ny, Nx;
   long long V;
-  int N, nst;
-  int radix[kMaxStages];
-  int W, LS;            // lines per tile, LDS line stride (float2)
-  long long lines;      // V / N
-  const float2* tw;     // exp(-2 pi i j / N)
+  const float2* tw;     // exp(-2 pi i j / N) of the x axis
   float sgn;            // -1: forward DFT, +1: inverse DFT
   int nb;               // pairs in this launch
   // sources
@@ -51,20 +45,9 @@ struct PassArgs {
   const float* tsc;      // 256^3 fp16 intermediates: scales of the writing workgroups [nb][1024]
   float* tsc_out;        // where the writing pass puts them
   int accumulate;        // SM_ACCUM: 1 adds to X, 0 overwrites
-  int phi_kind;          // SM_PHI: 0 identity, 1 |U|^phi_p sgn(U)
+  int phi_kind;          // phi_apply: 0 identity, 1 |U|^phi_p sgn(U)
   float phi_p;
 };
-
-__device__ __forceinline__ long long gaddr(const PassArgs& a, long long line, int n) {
-  if (a.axis == 2) return line * a.Nx + n;
-  if (a.axis == 1) {
-    long long z = line / a.Nx, x = line - z * a.Nx;
-    return (z * a.Ny + n) * a.Nx + x;
-  }
-  return (long long)n * a.Ny * a.Nx + line;
-}
-
-__device__ __forceinline__ int lidx(int LS, int w, int n) { return w * LS + n + (n >> 4); }
 
 // Non-temporal loads for values a pass streams through once (a plain read
 // kernel reaches 6.3 TB/s on this GPU, 7.0 TB/s with the hint).  Measured per
@@ -127,33 +110,6 @@ __device__ __forceinline__ void store_score(void* U, long long i, float2 v, floa
   }
 }
 
-// Fused first-pass load of element g (line position) for pair slot j.
-template <int LM, int DT = OS3D_C64>
-__device__ __forceinline__ float2 load_elem(const PassArgs& a, int j, long long g, float& asum) {
-  if constexpr (LM == LM_REAL) {
-    return make_float2(a.src_r[g], 0.f);
-  } else if constexpr (LM == LM_C) {
-    return a.src_c[j * a.src_stride + g];
-  } else if constexpr (LM == LM_MULBANK) {
-    const float p = a.psi[(long long)a.rows[j] * a.V + g] * a.kappa;
-    const float2 v = cscale(a.src_c[g], p);
-    if (a.partial) asum += sqrtf(v.x * v.x + v.y * v.y);  // scale bound of 16-bit storage only
-    return v;
-  } else if constexpr (LM == LM_UIN) {
-    const int ia = a.oa[j], ib = a.ob[j];
-    const float sa = a.scales ? a.scales[ia] : 1.f;
-    float2 v = load_score<DT>(a.U, (long long)ia * a.V + g, sa);
-    if (ib >= 0) {
-      const float sb = a.scales ? a.scales[ib] : 1.f;
-      v = cadd(v, cconj(load_score<DT>(a.U, (long long)ib * a.V + g, sb)));
-    }
-    return v;
-  } else {  // LM_DIVM
-    const float2 v = a.src_c[g];
-    return cscale(v, a.divide ? a.kappa / fmaxf(a.M[g], a.eps) : a.kappa);
-  }
-}
-
 // Phi of processing via scores applied to one transformed value v (times
 // out_scale = 1/V), times 2 for a stored antipodal pair: for real f the pair
 // contributes Phi(U_n) + conj(Phi(U_-n)) = 2 Phi(U_n) to the reconstruction.
@@ -176,61 +132,16 @@ __device__ __forceinline__ float2 phi_apply(const PassArgs& a, int j, float2 v) 
   return cscale(u, mult);
 }
 
-// Fused last-pass store of element g for pair slot j (SM_ACCUM adds into acc).
-template <int SM, int DT = OS3D_C64>
-__device__ __forceinline__ void store_elem(const PassArgs& a, int j, long long g, float2 v, float2& acc) {
-  if constexpr (SM == SM_C) {
-    a.dst_c[j * a.dst_stride + g] = v;
-  } else if constexpr (SM == SM_UOUT) {
-    const float2 u = cscale(v, a.out_scale);
-    const int ia = a.oa[j], ib = a.ob[j];
-    const float inv_s = a.scales ? 1.f / a.scales[ia] : 1.f;
-    store_score<DT>(a.Uout, (long long)ia * a.V + g, u, inv_s);
-    if (ib >= 0) store_score<DT>(a.Uout, (long long)ib * a.V + g, cconj(u), inv_s);
-  } else if constexpr (SM == SM_ACCUM) {
-    const float p = a.psi[(long long)a.rows[j] * a.V + g];
-    acc = make_float2(acc.x + p * v.x, acc.y + p * v.y);
-  } else if constexpr (SM == SM_PHI) {
-    a.dst_c[j * a.dst_stride + g] = phi_apply(a, j, v);
-  } else {  // SM_REAL
-    a.dst_r[g] = v.x * a.out_scale;
-  }
-}
-
-__device__ __forceinline__ void accum_flush(const PassArgs& a, long long g, float2 acc) {
-  float2 x = acc;
-  if (a.accumulate) x = cadd(a.dst_c[g], x);
-  a.dst_c[g] = x;
-}
-
-
 // K values of one thread at the affine positions g0 + r d (r < K), for pair
-// slot j.  Uniform conditions (partner present, division, scales) are
+// slot j (LM_REAL, LM_UIN, LM_DIVM; the others are loaded by their kernels).
+// Uniform conditions (partner present, division, scales) are
 // decided once, outside the unrolled loops, so that each group of loads sits
 // in one basic block and is issued back to back.
 template <int LM, int DT, int K>
-__device__ __forceinline__ void load_k(const PassArgs& a, int j, long long g0, long long d, float2 (&v)[K],
-                                       float& asum) {
+__device__ __forceinline__ void load_k(const PassArgs& a, int j, long long g0, long long d, float2 (&v)[K]) {
   if constexpr (LM == LM_REAL) {
 #pragma unroll
     for (int r = 0; r < K; ++r) v[r] = make_float2(a.src_r[g0 + r * d], 0.f);
-  } else if constexpr (LM == LM_C) {
-    const float2* p = a.src_c + j * a.src_stride;
-#pragma unroll
-    for (int r = 0; r < K; ++r) v[r] = ldnt(p + g0 + r * d);
-  } else if constexpr (LM == LM_MULBANK) {
-    const float* pr = a.psi + (long long)a.rows[j] * a.V;
-    float ps[K];
-#pragma unroll
-    for (int r = 0; r < K; ++r) ps[r] = ldnt(pr + g0 + r * d);
-#pragma unroll
-    for (int r = 0; r < K; ++r) v[r] = a.src_c[g0 + r * d];
-#pragma unroll
-    for (int r = 0; r < K; ++r) v[r] = cscale(v[r], ps[r] * a.kappa);
-    if (a.partial) {  // scale bound of 16-bit storage only
-#pragma unroll
-      for (int r = 0; r < K; ++r) asum += sqrtf(v[r].x * v[r].x + v[r].y * v[r].y);
-    }
   } else if constexpr (LM == LM_UIN) {
     const int ia = a.oa[j], ib = a.ob[j];
     float sa = 1.f, sb = 1.f;
@@ -292,11 +203,6 @@ __device__ __forceinline__ void store_k(const PassArgs& a, int j, long long g0, 
     for (int r = 0; r < K; ++r) ps[r] = ldnt(pr + g0 + r * d);
 #pragma unroll
     for (int r = 0; r < K; ++r) acc[r] = make_float2(acc[r].x + ps[r] * v[r].x, acc[r].y + ps[r] * v[r].y);
-  } else if constexpr (SM == SM_PHI) {
-    // the reconstruction's input for the pair (phi_apply)
-    float2* p = a.dst_c + j * a.dst_stride;
-#pragma unroll
-    for (int r = 0; r < K; ++r) p[g0 + r * d] = phi_apply(a, j, v[r]);
   } else {  // SM_REAL
 #pragma unroll
     for (int r = 0; r < K; ++r) a.dst_r[g0 + r * d] = v[r].x * a.out_scale;

@@ -1,4 +1,4 @@
-// In-register small DFTs for the Stockham passes (radix 2, 3, 4, 5, 8, 16).
+// In-register small DFTs of the passes (radix 2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16).
 // sgn = -1 gives the forward kernel exp(-2 pi i jk / R), +1 the inverse.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -104,6 +104,56 @@ __device__ __forceinline__ void dft16(float2* v, float sgn) {
 }
 
 template <int R>
+__device__ __forceinline__ void dft_r(float2* v, float sgn);
+
+// R = R1 R2 with coprime factors (Good-Thomas): with n = R2 n1 + R1 n2 (mod R)
+// and k = k1 (mod R1) = k2 (mod R2) the kernel splits into
+// W_R1^(n1 k1) W_R2^(n2 k2), so the two steps need no twiddles between them.
+template <int R1, int R2>
+__device__ __forceinline__ void dft_coprime(float2* v, float sgn) {
+  constexpr int R = R1 * R2;
+  float2 a[R1][R2];
+#pragma unroll
+  for (int n2 = 0; n2 < R2; ++n2) {
+    float2 c[R1];
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) c[n1] = v[(R2 * n1 + R1 * n2) % R];
+    dft_r<R1>(c, sgn);
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) a[n1][n2] = c[n1];
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) dft_r<R2>(a[k1], sgn);
+#pragma unroll
+  for (int k = 0; k < R; ++k) v[k] = a[k % R1][k % R2];
+}
+
+// 9 = 3 x 3: inner DFT3 over n1 (n = 3 n1 + n2), twiddle W9^(n2 k1), outer DFT3 (k = k1 + 3 k2).
+__device__ __forceinline__ void dft9(float2* v, float sgn) {
+  const float2 w1 = make_float2(0.766044443118978035202f, sgn * 0.642787609686539326323f);
+  const float2 w2 = make_float2(0.173648177666930348852f, sgn * 0.984807753012208059367f);
+  const float2 w4 = make_float2(-0.939692620785908384054f, sgn * 0.342020143325668733044f);
+  float2 c[3][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 3; ++n2) {
+    float2 u[3] = {v[n2], v[3 + n2], v[6 + n2]};
+    dft3(u, sgn);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) c[k1][n2] = u[k1];
+  }
+  c[1][1] = cmul(c[1][1], w1);
+  c[1][2] = cmul(c[1][2], w2);
+  c[2][1] = cmul(c[2][1], w2);
+  c[2][2] = cmul(c[2][2], w4);
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    dft3(c[k1], sgn);
+#pragma unroll
+    for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = c[k1][k2];
+  }
+}
+
+template <int R>
 __device__ __forceinline__ void dft_r(float2* v, float sgn) {
   if constexpr (R == 2) {
     dft2(v);
@@ -113,8 +163,18 @@ __device__ __forceinline__ void dft_r(float2* v, float sgn) {
     dft4(v[0], v[1], v[2], v[3], sgn);
   } else if constexpr (R == 5) {
     dft5(v, sgn);
+  } else if constexpr (R == 6) {
+    dft_coprime<2, 3>(v, sgn);
   } else if constexpr (R == 8) {
     dft8(v, sgn);
+  } else if constexpr (R == 9) {
+    dft9(v, sgn);
+  } else if constexpr (R == 10) {
+    dft_coprime<2, 5>(v, sgn);
+  } else if constexpr (R == 12) {
+    dft_coprime<4, 3>(v, sgn);
+  } else if constexpr (R == 15) {
+    dft_coprime<3, 5>(v, sgn);
   } else if constexpr (R == 16) {
     dft16(v, sgn);
   }

@@ -5,6 +5,8 @@
 // steering matrix of the rotated wavelets (Eqs. 17-19).
 #include <algorithm>
 #include <cmath>
+#include <numeric>
+#include <tuple>
 
 #include "os3d_internal.h"
 
@@ -379,34 +381,30 @@ bool factor235(int64_t n) {
   return n == 1;
 }
 
-// Radix schedule of a length-n DFT: powers of two in factors of 16 (then 8,
-// 4, 2), then 5s and 3s.  The product of the radices is n.
+// Factors of a length-n DFT from {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2}: as few
+// as possible (each costs a round trip through LDS), then the largest smallest
+// factor (a line kernel runs n / R_min butterflies side by side), then the
+// smallest sum; in descending order.
 std::vector<int> radix_schedule(int n) {
-  std::vector<int> r;
-  int m = n;
-  int p2 = 0;
-  while (m % 2 == 0) {
-    m /= 2;
-    ++p2;
-  }
-  while (m % 5 == 0) {
-    r.push_back(5);
-    m /= 5;
-  }
-  while (m % 3 == 0) {
-    r.push_back(3);
-    m /= 3;
-  }
-  std::vector<int> r2;
-  while (p2 >= 4) {
-    r2.push_back(16);
-    p2 -= 4;
-  }
-  if (p2 == 3) r2.push_back(8);
-  if (p2 == 2) r2.push_back(4);
-  if (p2 == 1) r2.push_back(2);
-  r2.insert(r2.end(), r.begin(), r.end());
-  return r2;
+  std::vector<int> best, cur;
+  auto search = [&](auto self, int m, int maxr) -> void {
+    if (m == 1) {
+      auto key = [](const std::vector<int>& r) {
+        return std::make_tuple((int)r.size(), r.empty() ? 0 : -r.back(), std::accumulate(r.begin(), r.end(), 0));
+      };
+      if (best.empty() || key(cur) < key(best)) best = cur;
+      return;
+    }
+    if ((int)cur.size() == kMaxStages) return;
+    for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2})
+      if (r <= maxr && m % r == 0) {
+        cur.push_back(r);
+        self(self, m / r, r);
+        cur.pop_back();
+      }
+  };
+  search(search, n, 16);
+  return best;
 }
 
 }  // namespace os3d

@@ -141,8 +141,7 @@ __global__ __launch_bounds__(k4Threads) void k4_inv_phi(PassArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) spec[r] = cscale(a.src_c[base + t + r * 1024], a.kappa);
   } else {
-    float unused = 0.f;
-    load_k<LM, OS3D_C64, 16>(a, 0, base + t, 1024, spec, unused);
+    load_k<LM, OS3D_C64, 16>(a, 0, base + t, 1024, spec);
   }
   float pnx[16];
   if constexpr (LM == LM_MULBANK) {
@@ -407,8 +406,7 @@ __global__ __launch_bounds__(k4Threads) void k4_fwd_nat(PassArgs a) {
   const int j = blockIdx.y;
   load_twiddles<-1>(a, twl);
   float2 v[16];
-  float asum = 0.f;
-  load_k<LM, DT, 16>(a, j, fwd_nat_row(blockIdx.x) + (threadIdx.x & 15), 16, v, asum);
+  load_k<LM, DT, 16>(a, j, fwd_nat_row(blockIdx.x) + (threadIdx.x & 15), 16, v);
   fwd_nat_tile<T16>(a, lds, twl, red, j, blockIdx.x, v);
 }
 
@@ -623,7 +621,6 @@ static PassArgs base_args(const os3d_bank* b, float sgn) {
   PassArgs a = {};
   a.Nz = a.Ny = a.Nx = 256;
   a.V = b->V;
-  a.N = 256;
   a.tw = (const float2*)b->d.tw[0];
   a.sgn = sgn;
   a.nb = 1;

@@ -1,0 +1,623 @@
+// Line passes of the general transform: the z lines with the spectral
+// multiply, the orientation sum and the division fused in, and the y lines
+// of volumes whose (y, x) planes do not fit in LDS (stages: fft_tile.h).
+//
+// A workgroup owns W neighbouring lines (consecutive x, so every access is a
+// run of W values).  Each thread holds one butterfly: the first stage loads
+// its inputs straight from memory and the last stage hands its outputs over
+// in registers, so a two-factor line makes one LDS round trip.  The passes
+// are bound by memory (a value costs one 8-byte read or write, its bank row
+// entry and about 70 flops): the spectrum of a tile (k_line_mul) or its
+// orientation sum (k_line_acc) stays in registers over the pairs of a launch.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <mutex>
+#include <set>
+
+#include "fft_tile.h"
+#include "launch.h"
+
+namespace os3d {
+
+typedef unsigned short u16;
+
+// One workgroup's LDS: the tile [position][W], twiddles, frequency of each position.
+struct LineTile {
+  float2* buf;
+  float2* tw;
+  u16* fq;
+  float* red;
+  int b, c, lw;  // butterfly, line of this thread
+};
+
+__device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
+  const AxisT& z = a.y;
+  LineTile t;
+  t.lw = a.lw;
+  t.c = threadIdx.x & ((1 << a.lw) - 1);
+  t.b = threadIdx.x >> a.lw;
+  t.buf = lds;
+  t.tw = lds + (z.N << a.lw);
+  t.fq = (u16*)(t.tw + z.N);
+  t.red = (float*)(t.fq + ((z.N + 1) & ~1));
+  for (int i = threadIdx.x; i < z.N; i += blockDim.x) {
+    t.tw[i] = z.tw[i];
+    t.fq[i] = (u16)freq_of(z, i);
+  }
+  __syncthreads();
+  return t;
+}
+
+// The stages between the first and the last factor are chosen at run time;
+// the last factor RL is a template parameter of the kernels, because its
+// butterflies' values live in registers across the stages.
+
+// The thread's butterfly, opaque to the compiler: it otherwise moves the
+// addresses of every radix out of the loop over the pairs and spills them.
+__device__ __forceinline__ int butterfly(const LineTile& t) {
+  int b = t.b;
+  asm volatile("" : "+v"(b));
+  return b;
+}
+
+// The thread's butterfly of the last factor.  Threads past the last one
+// repeat the first (and store nothing): a branch around values that live
+// across the stages would cost a second copy of them.
+template <int RL>
+__device__ __forceinline__ int last_butterfly(const AxisT& z, const LineTile& t) {
+  const int b = butterfly(t);
+  return b * RL < z.N ? b : 0;
+}
+template <int RL>
+__device__ __forceinline__ bool has_last(const AxisT& z, const LineTile& t) {
+  return butterfly(t) * RL < z.N;
+}
+
+// DIF of the tile: src(o) gives the thread's line at offset o = n dn (point n);
+// out[r] receives frequency fq[b RL] + r N / RL of its last butterfly b.
+// Offsets are a thread's base plus a scalar per value.  mid() runs after the
+// first stage (its loads then don't hold registers next to that stage's).
+template <bool INV, int RL, class Src, class Mid>
+__device__ __forceinline__ void line_dif(const AxisT& z, const LineTile& t, long long dn, Src src, Mid mid,
+                                         float2 (&out)[RL]) {
+  constexpr float sg = INV ? 1.f : -1.f;
+  const int last = z.nst - 1, b = butterfly(t);
+  if (last == 0) {
+#pragma unroll
+    for (int r = 0; r < RL; ++r) out[r] = src(r * dn);
+    dft_r<RL>(out, sg);
+    mid();
+    return;
+  }
+  if (b < z.S[0]) {
+    with_radix(z.R[0], OS3D_RADIX_FN(rc) {
+      constexpr int R = decltype(rc)::value;
+      float2 v[R];
+      const long long o = b * dn, step = z.S[0] * dn;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = src(o + r * step);
+      dft_r<R>(v, sg);
+      float2* q = t.buf + (b << t.lw) + t.c;
+      const int d = z.S[0] << t.lw;
+#pragma unroll
+      for (int r = 0; r < R; ++r) q[r * d] = v[r];
+    });
+  }
+  mid();
+  __syncthreads();
+  for (int i = 1; i < last; ++i) {
+    const int S = z.S[i], u = fdiv(b, z.mS[i]), l = b - u * S;
+    with_radix(z.R[i], OS3D_RADIX_FN(rc) {
+      constexpr int R = decltype(rc)::value;
+      if (u * R * S < z.N) {
+        float2* q = t.buf + ((u * R * S + l) << t.lw) + t.c;
+        const int d = S << t.lw;
+        float2 v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = q[r * d];
+        twiddle<R, INV>(v, t.tw, t.fq[u * R * S] * S);
+        dft_r<R>(v, sg);
+#pragma unroll
+        for (int r = 0; r < R; ++r) q[r * d] = v[r];
+      }
+    });
+    __syncthreads();
+  }
+  {
+    const int p = last_butterfly<RL>(z, t) * RL;
+    const float2* q = t.buf + (p << t.lw) + t.c;
+    const int d = 1 << t.lw;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) out[r] = q[r * d];
+    twiddle<RL, INV>(out, t.tw, t.fq[p]);
+    dft_r<RL>(out, sg);
+  }
+}
+
+// DIT of the tile from the registers of the last factor's butterflies;
+// sink(o, v) takes the value at offset o = n dn of the thread's line.  The
+// caller synchronises before the tile's LDS is written again.
+template <bool INV, int RL, class Sink>
+__device__ __forceinline__ void line_dit(const AxisT& z, const LineTile& t, long long dn, float2 (&in)[RL],
+                                         Sink sink) {
+  constexpr float sg = INV ? 1.f : -1.f;
+  const int last = z.nst - 1, b = butterfly(t);
+  dft_r<RL>(in, sg);
+  if (b * RL < z.N) {
+    if (last == 0) {
+#pragma unroll
+      for (int r = 0; r < RL; ++r) sink(r * dn, in[r]);
+    } else {
+      float2* q = t.buf + ((b * RL) << t.lw) + t.c;
+      const int d = 1 << t.lw;
+#pragma unroll
+      for (int r = 0; r < RL; ++r) q[r * d] = in[r];
+    }
+  }
+  for (int i = last - 1; i >= 0; --i) {
+    __syncthreads();
+    const int S = z.S[i], u = fdiv(b, z.mS[i]), l = b - u * S;
+    with_radix(z.R[i], OS3D_RADIX_FN(rc) {
+      constexpr int R = decltype(rc)::value;
+      if (u * R * S < z.N) {
+        float2* q = t.buf + ((u * R * S + l) << t.lw) + t.c;
+        const int d = S << t.lw;
+        float2 v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = q[r * d];
+        twiddle<R, INV>(v, t.tw, l * z.tstep[i]);
+        dft_r<R>(v, sg);
+        if (i == 0) {
+          const long long o = l * dn, step = S * dn;
+#pragma unroll
+          for (int r = 0; r < R; ++r) sink(o + r * step, v[r]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < R; ++r) q[r * d] = v[r];
+        }
+      }
+    });
+  }
+}
+
+// get(r, o) for the frequencies k of the thread's last-factor butterfly, at offsets o = k dn
+template <int RL, class Get>
+__device__ __forceinline__ void each_freq(const AxisT& z, const LineTile& t, long long dn, Get get) {
+  const long long o = t.fq[last_butterfly<RL>(z, t) * RL] * dn, step = (z.N / RL) * dn;
+#pragma unroll
+  for (int r = 0; r < RL; ++r) get(r, o + r * step);
+}
+
+// The DFT of f along z (f transformed along y and x), then for every pair:
+// times the bank row, inverse DFT along z -> intermediate (complex64
+// scores and processing; 16-bit scores: k_line_mul_seq).
+template <int RL>
+__global__ __launch_bounds__(1024) void k_line_mul(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const AxisT& z = a.y;
+  const LineTile t = line_tile(a, lds);
+  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
+  const bool valid = line < a.lines;
+  const long long col = valid ? line : a.lines - 1;
+  float2 spec[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) spec[r] = make_float2(0.f, 0.f);
+  line_dif<false>(z, t, a.dn, [&](long long o) { return p.src_c[o + col]; }, []() {}, spec);
+  float ps[RL];
+  const int j0 = (int)((long long)p.nb * blockIdx.y / a.groups);
+  const int j1 = (int)((long long)p.nb * (blockIdx.y + 1) / a.groups);
+  {
+    const float* row = p.psi + (long long)p.rows[j0] * p.V + col;
+    each_freq<RL>(z, t, a.dn, [&](int r, long long o) {
+      ps[r] = row[o];
+      spec[r] = cscale(spec[r], p.kappa);
+    });
+  }
+  for (int j = j0; j < j1; ++j) {
+    float2 v[RL];
+#pragma unroll
+    for (int r = 0; r < RL; ++r) v[r] = cscale(spec[r], ps[r]);
+    if (j + 1 < j1) {
+      const float* row = p.psi + (long long)p.rows[j + 1] * p.V + col;
+      each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = row[o]; });
+    }
+    __syncthreads();  // the previous pair's reads of the tile are done
+    float2* T = p.dst_c + (long long)j * p.dst_stride + col;
+    line_dit<true>(z, t, a.dn, v, [&](long long o, float2 w) {
+      if (valid) T[o] = w;
+    });
+  }
+}
+
+// in *= kappa / max(M, eps) (kappa alone for the adjoint), then the inverse DFT along z -> dst.
+template <int RL>
+__device__ __forceinline__ void divide_inverse(const TileArgs& a, const LineTile& t, float2 (&x)[RL], long long col,
+                                               bool valid) {
+  const PassArgs& p = a.p;
+  if (p.divide) {
+    const float* M = p.M + col;
+    each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { x[r] = cscale(x[r], p.kappa / fmaxf(M[o], p.eps)); });
+  } else {
+#pragma unroll
+    for (int r = 0; r < RL; ++r) x[r] = cscale(x[r], p.kappa);
+  }
+  __syncthreads();
+  float2* X = p.dst_c + col;
+  line_dit<true>(a.y, t, a.dn, x, [&](long long o, float2 w) {
+    if (valid) X[o] = w;
+  });
+}
+
+// DFT along z of every pair's intermediate, times its bank row, summed over
+// the workgroup's share of the pairs.  With few lines the pairs of a launch
+// are shared out to `groups` workgroups per tile (a volume of partial sums
+// each, added by k_line_div): 64^3 x 21 pairs has 128 tiles for 256 CUs.
+template <int RL>
+__global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const AxisT& z = a.y;
+  const LineTile t = line_tile(a, lds);
+  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
+  const bool valid = line < a.lines;
+  const long long col = valid ? line : a.lines - 1;
+  float2 acc[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) acc[r] = make_float2(0.f, 0.f);
+  const int g = blockIdx.y;
+  const int j0 = (int)((long long)p.nb * g / a.groups), j1 = (int)((long long)p.nb * (g + 1) / a.groups);
+  for (int j = j0; j < j1; ++j) {
+    const float* row = p.psi + (long long)p.rows[j] * p.V + col;
+    const float2* T = p.src_c + (long long)j * p.src_stride + col;
+    float ps[RL];
+    float2 v[RL];
+    if (j > j0) __syncthreads();  // the previous pair's reads of the tile are done
+    line_dif<false>(
+        z, t, a.dn, [&](long long o) { return ldnt(T + o); },
+        [&]() { each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = ldnt(row + o); }); }, v);
+    each_freq<RL>(z, t, a.dn, [&](int r, long long) {
+      acc[r] = make_float2(acc[r].x + ps[r] * v[r].x, acc[r].y + ps[r] * v[r].y);
+    });
+  }
+  float2* X = (g == 0 ? p.dst_c : const_cast<float2*>(a.part) + (long long)(g - 1) * p.V) + col;
+  if (p.accumulate) each_freq<RL>(z, t, a.dn, [&](int r, long long o) { acc[r] = cadd(X[o], acc[r]); });
+  if (a.finish) {
+    divide_inverse(a, t, acc, col, valid);
+  } else if (valid && has_last<RL>(z, t)) {
+    each_freq<RL>(z, t, a.dn, [&](int r, long long o) { X[o] = acc[r]; });
+  }
+}
+
+// The partial orientation sums added up, divided by M, inverse DFT along z.
+template <int RL>
+__global__ __launch_bounds__(1024) void k_line_div(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const LineTile t = line_tile(a, lds);
+  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
+  const bool valid = line < a.lines;
+  const long long col = valid ? line : a.lines - 1;
+  float2 x[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) x[r] = make_float2(0.f, 0.f);
+  each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { x[r] = p.src_c[o + col]; });
+  for (int g = 0; g < a.nparts; ++g) {
+    const float2* X = a.part + (long long)g * p.V + col;
+    each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { x[r] = cadd(x[r], X[o]); });
+  }
+  divide_inverse(a, t, x, col, valid);
+}
+
+// DFT of the y lines of every pair's volume, in place or from src to dst.
+template <bool INV, int RL>
+__global__ __launch_bounds__(1024) void k_line_y(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const AxisT& y = a.y;
+  const LineTile t = line_tile(a, lds);
+  const int zp = blockIdx.x / a.chunks, x = ((blockIdx.x - zp * a.chunks) << a.lw) + t.c;
+  const bool valid = x < p.Nx;
+  const long long col = (long long)zp * p.Ny * p.Nx + (valid ? x : p.Nx - 1);
+  const float2* src = p.src_c + (long long)blockIdx.y * p.src_stride + col;
+  float2* dst = p.dst_c + (long long)blockIdx.y * p.dst_stride + col;
+  float2 v[RL];
+  line_dif<INV>(y, t, a.dn, [&](long long o) { return ldnt(src + o); }, []() {}, v);
+  if (y.nst > 1) __syncthreads();
+  if (valid && has_last<RL>(y, t)) each_freq<RL>(y, t, a.dn, [&](int r, long long o) { dst[o] = v[r]; });
+}
+
+// ---------------------------------------------------------------- 16-bit scores
+// The same passes in the sequential order (fft_tile.h), DIF in both
+// directions.
+
+// Stages after the first; sink(o, v) takes frequency k at offset o = k dn, or,
+// TO_LDS, the tile keeps the values at their digit-reversed positions.
+template <bool TO_LDS, class Sink>
+__device__ __forceinline__ void line_seq_rest(const AxisT& z, const LineTile& t, long long dn, float sgn, Sink sink) {
+  const int nbt = blockDim.x >> t.lw;
+  for (int i = 1; i < z.nst; ++i) {
+    __syncthreads();
+    const int S = z.S[i];
+    const bool last = i == z.nst - 1;
+    with_seq(z.R[i], z.RB[i], OS3D_SEQ_FN(rc, rb) {
+      constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
+      for (int b = butterfly(t); b < z.nb[i]; b += nbt) {
+        const int u = fdiv(b, z.mS[i]), l = b - u * S;
+        float2* q = t.buf + ((u * R * S + l) << t.lw) + t.c;
+        const int d = S << t.lw, f = t.fq[u * R * S];
+        float2 v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = q[r * d];
+        seq_butterfly<R, RB>(v, t.tw, f, S, z.tstep[i], false, sgn);
+        if (TO_LDS || !last) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) q[r * d] = v[r];
+        } else {
+          const long long o = f * dn, step = z.tstep[i] * dn;
+#pragma unroll
+          for (int r = 0; r < R; ++r) sink(o + seq_slot<R, RB>(r) * step, v[r]);
+        }
+      }
+    });
+  }
+}
+
+// Conjugates the tile's twiddles (between barriers).
+__device__ __forceinline__ void conj_twiddles(const AxisT& z, const LineTile& t) {
+  for (int i = threadIdx.x; i < z.N; i += blockDim.x) t.tw[i].y = -t.tw[i].y;
+}
+
+// k_line_mul for 16-bit scores, with the sums of |value| of their scale
+// bound.  (R0, RB0): the first stage, whose inputs (the tile's spectrum) stay
+// in registers over the pairs.
+template <int R0, int RB0>
+__global__ __launch_bounds__(1024) void k_line_mul_seq(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const AxisT& z = a.y;
+  const LineTile t = line_tile(a, lds);
+  u16* pos = (u16*)(t.red + 16);  // position of a frequency
+  for (int i = threadIdx.x; i < z.N; i += blockDim.x) pos[t.fq[i]] = (u16)i;
+  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
+  const bool valid = line < a.lines;
+  const long long col = valid ? line : a.lines - 1;
+  const bool first = t.b < z.S[0];
+  const int b0 = first ? t.b : 0;
+  float2 spec[R0];
+  const long long o0 = b0 * a.dn, step0 = z.S[0] * a.dn;
+#pragma unroll
+  for (int r = 0; r < R0; ++r) spec[r] = p.src_c[o0 + r * step0 + col];
+  seq_butterfly<R0, RB0>(spec, t.tw, 0, z.S[0], 1, true, -p.sgn);
+  float2* q0 = t.buf + (b0 << t.lw) + t.c;
+  const int d0 = z.S[0] << t.lw;
+  if (first) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) q0[r * d0] = spec[r];
+  }
+  line_seq_rest<true>(z, t, a.dn, -p.sgn, [](long long, float2) {});
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < R0; ++r) spec[r] = t.buf[(pos[b0 + r * z.S[0]] << t.lw) + t.c];
+  conj_twiddles(z, t);
+  const int j0 = (int)((long long)p.nb * blockIdx.y / a.groups);
+  const int j1 = (int)((long long)p.nb * (blockIdx.y + 1) / a.groups);
+  float ps[R0];
+  {
+    const float* row = p.psi + (long long)p.rows[j0] * p.V + col;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) ps[r] = row[o0 + r * step0];
+  }
+  for (int j = j0; j < j1; ++j) {
+    float2 v[R0];
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      v[r] = cscale(spec[r], ps[r] * p.kappa);
+      hold(v[r]);
+    }
+    if (j + 1 < j1) {
+      const float* row = p.psi + (long long)p.rows[j + 1] * p.V + col;
+#pragma unroll
+      for (int r = 0; r < R0; ++r) ps[r] = row[o0 + r * step0];
+    }
+    // the hardware square root (1 ulp) is ample for a bound that is rounded
+    // up to a power of two
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) s += __builtin_amdgcn_sqrtf(v[r].x * v[r].x + v[r].y * v[r].y);
+    if (!valid || !first) s = 0.f;
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    __syncthreads();  // the previous pair's reads of the tile (and of red) are done
+    if ((threadIdx.x & 63) == 0) t.red[threadIdx.x >> 6] = s;
+    seq_butterfly<R0, RB0>(v, t.tw, 0, z.S[0], 1, true, p.sgn);
+    float2* T = p.dst_c + (long long)j * p.dst_stride + col;
+    if (z.nst > 1) {
+      if (first) {
+#pragma unroll
+        for (int r = 0; r < R0; ++r) q0[r * d0] = v[r];
+      }
+    } else if (first && valid) {
+#pragma unroll
+      for (int r = 0; r < R0; ++r) T[seq_slot<R0, RB0>(r) * a.dn] = v[r];
+    }
+    line_seq_rest<false>(z, t, a.dn, p.sgn, [&](long long o, float2 w) {
+      if (valid) T[o] = w;
+    });
+    if (z.nst == 1) __syncthreads();
+    if (threadIdx.x == 0) {
+      float sum = 0.f;
+      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) sum += t.red[w];
+      p.partial[(long long)j * gridDim.x + blockIdx.x] = sum;
+    }
+  }
+}
+
+// DFT of the y lines of every pair's volume, in place or from src to dst.
+__global__ __launch_bounds__(1024) void k_line_y_seq(TileArgs a) {
+  extern __shared__ float2 lds[];
+  const PassArgs& p = a.p;
+  const AxisT& y = a.y;
+  const LineTile t = line_tile(a, lds);
+  if (p.sgn > 0.f) conj_twiddles(y, t);
+  const int zp = blockIdx.x / a.chunks, x = ((blockIdx.x - zp * a.chunks) << a.lw) + t.c;
+  const bool valid = x < p.Nx;
+  const long long col = (long long)zp * p.Ny * p.Nx + (valid ? x : p.Nx - 1);
+  const float2* src = p.src_c + (long long)blockIdx.y * p.src_stride + col;
+  float2* dst = p.dst_c + (long long)blockIdx.y * p.dst_stride + col;
+  if (t.b < y.S[0]) {
+    with_seq(y.R[0], y.RB[0], OS3D_SEQ_FN(rc, rb) {
+      constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
+      float2 v[R];
+      const long long o = t.b * a.dn, step = y.S[0] * a.dn;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = ldnt(src + o + r * step);
+      seq_butterfly<R, RB>(v, t.tw, 0, y.S[0], 1, true, p.sgn);
+      if (y.nst > 1) {
+        float2* q = t.buf + (t.b << t.lw) + t.c;
+        const int d = y.S[0] << t.lw;
+#pragma unroll
+        for (int r = 0; r < R; ++r) q[r * d] = v[r];
+      } else if (valid) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) dst[seq_slot<R, RB>(r) * a.dn] = v[r];
+      }
+    });
+  }
+  line_seq_rest<false>(y, t, a.dn, p.sgn, [&](long long o, float2 w) {
+    if (valid) dst[o] = w;
+  });
+}
+
+// ---------------------------------------------------------------- host side
+// Raises the dynamic-LDS limit of a kernel once.
+static void reserve_lds(const void* kernel) {
+  static std::mutex mu;
+  static std::set<const void*> done;
+  std::lock_guard<std::mutex> lock(mu);
+  if (done.insert(kernel).second)
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+}
+
+static int check_line(const char* what) {
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    set_error(std::string(what) + ": " + hipGetErrorString(e));
+    return OS3D_EDEVICE;
+  }
+  return OS3D_OK;
+}
+
+struct LinePlan {
+  int lw, threads;
+  size_t lds;
+};
+
+template <class K>
+static void launch_line(K kernel, dim3 grid, const LinePlan& q, const TileArgs& a, hipStream_t st) {
+  reserve_lds((const void*)kernel);
+  launch_k(kernel, grid, dim3(q.threads), (unsigned)q.lds, st, a);
+}
+
+// Lines per workgroup: as many as fill 512 threads with one butterfly each
+// (up to 64 KB of tile, two workgroups per CU), at least runs of 16 values
+// where 1024 threads allow; fewer (down to 16) while the grid is smaller than
+// two workgroups per CU.
+static LinePlan line_plan(const AxisT& z, long long lines) {
+  int rmin = 16;
+  for (int i = 0; i < z.nst; ++i) rmin = std::min(rmin, z.R[i]);
+  const int nbf = z.N / rmin;
+  int lw = 0;
+  while (lw < 8 && (2 << lw) * nbf <= 512 && (2 << lw) * z.N <= 8192) ++lw;
+  while (lw < 4 && (2 << lw) * nbf <= 1024 && (2 << lw) * z.N <= 8192) ++lw;
+  while (lw > 4 && ((lines + (1 << lw) - 1) >> lw) < 512) --lw;
+  LinePlan q;
+  q.lw = lw;
+  q.threads = std::min(1024, ((nbf << lw) + 63) / 64 * 64);
+  q.lds = ((size_t)z.N << lw) * 8 + (size_t)z.N * 8 + (size_t)((z.N + 1) & ~1) * 4 + 64;
+  return q;
+}
+
+static TileArgs zline_args(const os3d_bank* b, const PassArgs& p, LinePlan& q, bool seq = false) {
+  TileArgs a = {};
+  a.p = p;
+  a.y = seq ? make_axis_seq((int)b->dims[0], b->d.tw[0]) : make_axis((int)b->dims[0], b->d.tw[0]);
+  a.lines = b->dims[1] * b->dims[2];
+  a.dn = a.lines;
+  q = line_plan(a.y, a.lines);
+  a.lw = q.lw;
+  a.chunks = (int)((a.lines + (1LL << q.lw) - 1) >> q.lw);
+  a.groups = 1;
+  return a;
+}
+
+int zline_tiles(const os3d_bank* b, bool seq) {
+  LinePlan q;
+  return zline_args(b, PassArgs{}, q, seq).chunks;
+}
+
+int zline_acc_groups(const os3d_bank* b, int nb) {
+  const int tiles = zline_tiles(b, false);
+  return std::max(1, std::min(std::min(8, nb / 2), 512 / std::max(1, tiles)));
+}
+
+int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
+  LinePlan q;
+  const bool seq = p.partial != nullptr;
+  TileArgs a = zline_args(b, p, q, seq);
+  // the forward DFT is repeated by every workgroup of a tile: share the
+  // pairs only as far as it takes to fill the chip
+  a.groups = std::max(1, std::min(p.nb, (1024 + a.chunks - 1) / a.chunks));
+  const dim3 grid((unsigned)a.chunks, (unsigned)a.groups);
+  if (seq)
+    with_seq(a.y.R[0], a.y.RB[0], [&](auto rc, auto rb) {
+      launch_line(k_line_mul_seq<decltype(rc)::value, decltype(rb)::value>, grid, q, a, st);
+    });
+  else
+    with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_mul<decltype(rc)::value>, grid, q, a, st); });
+  return check_line("k_line_mul");
+}
+
+int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* parts, int groups, bool finish, hipStream_t st) {
+  LinePlan q;
+  TileArgs a = zline_args(b, p, q);
+  a.groups = groups;
+  a.part = parts;
+  a.finish = finish ? 1 : 0;
+  const dim3 grid((unsigned)a.chunks, (unsigned)a.groups);
+  with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_acc<decltype(rc)::value>, grid, q, a, st); });
+  return check_line("k_line_acc");
+}
+
+int launch_zline_div(const os3d_bank* b, const PassArgs& p, const float2* parts, int nparts, hipStream_t st) {
+  LinePlan q;
+  TileArgs a = zline_args(b, p, q);
+  a.part = parts;
+  a.nparts = nparts;
+  const dim3 grid((unsigned)a.chunks);
+  with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_div<decltype(rc)::value>, grid, q, a, st); });
+  return check_line("k_line_div");
+}
+
+int launch_yline(const os3d_bank* b, const PassArgs& p, bool seq, hipStream_t st) {
+  TileArgs a = {};
+  a.p = p;
+  a.y = seq ? make_axis_seq((int)b->dims[1], b->d.tw[1]) : make_axis((int)b->dims[1], b->d.tw[1]);
+  a.dn = b->dims[2];
+  a.lines = b->dims[0] * b->dims[2];
+  const LinePlan q = line_plan(a.y, a.lines);
+  a.lw = q.lw;
+  a.chunks = (int)((b->dims[2] + (1LL << q.lw) - 1) >> q.lw);
+  const dim3 grid((unsigned)(a.chunks * b->dims[0]), (unsigned)p.nb);
+  if (seq) {
+    launch_line(k_line_y_seq, grid, q, a, st);
+    return check_line("k_line_y_seq");
+  }
+  with_radix(a.y.R[a.y.nst - 1], [&](auto rc) {
+    constexpr int RL = decltype(rc)::value;
+    launch_line(p.sgn > 0.f ? k_line_y<true, RL> : k_line_y<false, RL>, grid, q, a, st);
+  });
+  return check_line("k_line_y");
+}
+
+}  // namespace os3d

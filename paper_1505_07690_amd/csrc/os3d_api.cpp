@@ -190,7 +190,10 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   b->Npad = (b->n_unique + 15) / 16 * 16;
   // 256^3 volumes take the two-pass transform and its frequency tiles
   b->layout = (dims[0] == 256 && dims[1] == 256 && dims[2] == 256) ? 1 : 0;
-  b->plane = (b->layout == 0 && dims[1] == dims[2] && (dims[2] == 64 || dims[2] == 128)) ? 1 : 0;
+  if (b->layout == 0)
+    b->plane = (dims[1] == dims[2] && (dims[2] == 64 || dims[2] == 128)) ? kPlaneFixed
+               : plane_fits((int)dims[1], (int)dims[2])                  ? kPlaneTile
+                                                                         : kPlaneNone;
   if (const char* e = std::getenv("OS3D_THREE_PASS"))
     if (e[0] == '1') b->layout = b->plane = 0;
   const BankLayout lay = layout(dims, b->n_unique, p->L);
@@ -208,12 +211,6 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   b->d.tab = (double*)(base + lay.tab);
   b->d.part = (double*)(base + lay.part);
   for (int d = 0; d < 3; ++d) b->d.tw[d] = (float*)(base + lay.tw[d]);
-  for (int d = 0; d < 3; ++d) {
-    std::vector<int> r = radix_schedule((int)dims[d]);
-    b->plan[d].n = (int)dims[d];
-    b->plan[d].nstages = (int)r.size();
-    for (int s = 0; s < kMaxStages; ++s) b->plan[d].radix[s] = s < (int)r.size() ? r[s] : 0;
-  }
 
   // host FP64 design: coefficients, steering matrix as MFMA operands, recursion tables, twiddles
   std::vector<double> c, a;

@@ -16,7 +16,6 @@ constexpr int kMaxBankL = 62;
 
 constexpr int kMaxL = 64;
 constexpr int kMaxDim = 4096;
-constexpr int kMaxStages = 14;
 
 // ---------------------------------------------------------------- host FP64 setup
 double bspline(int k, double x);
@@ -66,14 +65,13 @@ void steering_std(const os3d_wavelet_params& p, const double* orients, int n, co
 void pair_orientations(const double* orients, int n, std::vector<int>& partner);
 
 bool factor235(int64_t n);
-std::vector<int> radix_schedule(int n);  // radices in {16, 8, 4, 2, 5, 3}
+constexpr int kMaxStages = 5;            // of any length up to kMaxDim
+std::vector<int> radix_schedule(int n);  // at most kMaxStages factors <= 16
 
 // ---------------------------------------------------------------- device plan
-struct AxisPlan {
-  int n;
-  int nstages;
-  int radix[kMaxStages];
-};
+// Passes over the (y, x) planes: y lines then x lines, whole planes of 64^2 or
+// 128^2 (kernels_plane.hip), whole planes of any other size that fits in LDS.
+enum PlanePath { kPlaneNone = 0, kPlaneFixed = 1, kPlaneTile = 2 };
 
 struct DevPtrs {
   float* psi;      // [n_unique][V] float32 g h without kappa (the transforms apply kappa)
@@ -95,7 +93,7 @@ struct os3d_bank {
   int n_unique;
   int paired;
   int layout;                 // frequency storage order: 0 natural, 1 four-step tiles of 256^3
-  int plane;                  // natural order with Ny = Nx in {64, 128}: z-line pass + whole-plane pass
+  int plane;                  // natural order: how the (y, x) planes are transformed (PlanePath)
   int L;
   int Npad;
   int kblocks;                // K-blocks of the synthesis contraction
@@ -109,7 +107,6 @@ struct os3d_bank {
   std::vector<int> row_of;    // per orientation: stored bank row
   std::vector<int> conj_of;   // per orientation: 1 when it is the second member of a pair (psi(Sk))
   std::vector<int> rep;       // per stored row: orientation index of the stored member
-  os3d::AxisPlan plan[3];     // z, y, x
   os3d::DevPtrs d;
   void* base;
   size_t bytes;
@@ -134,6 +131,7 @@ int launch_approx(const os3d_bank* b, const void* U, int dtype, const float* sca
                   void* stream);
 int launch_export_M(const os3d_bank* b, float* out, void* stream);
 size_t workspace_bytes(const os3d_bank* b);
+bool plane_fits(int Ny, int Nx);  // a (y, x) plane fits in LDS
 int profile_enable(int on);
 // Launch bracketing for the per-kernel timer: prof_start returns a token (or
 // null when timing is off) and leaves its events for the one launch that

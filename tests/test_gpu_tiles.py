@@ -1,0 +1,71 @@
+"""The mixed-radix line, plane and tile kernels at the sizes where their plans
+change, against the FP64 oracle: planes just inside and past LDS, axes of one
+to five factors, odd and even last factors, tiles with a ragged edge, and pair
+sums shared by several workgroups over several launches.  FP32 paths: relative
+L2 error <= 1e-5 (the bound of every FP32 path); 16-bit scores: the storage
+bound, and the reconstruction of the dequantised scores to 1e-5 (complex64
+intermediates)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1505_07690_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5
+
+
+def rel(a, b):
+    a, b = np.asarray(a), np.asarray(b)
+    return float(np.linalg.norm((a - b).ravel()) / np.linalg.norm(b.ravel()))
+
+
+def _random_orients(n, seed):
+    v = np.random.default_rng(seed).standard_normal((n, 3))
+    return v / np.linalg.norm(v, axis=1, keepdims=True)
+
+
+SHAPES = {
+    "plane_19200_of_lds": ((4, 128, 150), "octahedron"),   # 15 x 10 rows, 19 values per thread
+    "plane_past_lds": ((5, 180, 150), "octahedron"),       # y lines and x lines, ragged x chunks
+    "padded_rows_past_lds": ((3, 160, 128), "octahedron"),  # 20480 values, but padded rows
+    "x_one_factor": ((9, 60, 16), "tetrahedron"),
+    "y_one_factor": ((16, 12, 225), "tetrahedron"),
+    "z_three_factors": ((250, 6, 10), "octahedron"),
+    "z_five_factors": ((3125, 2, 4), "octahedron"),
+    "y_4050": ((2, 4050, 3), "tetrahedron"),
+    "x_4096": ((3, 2, 4096), "octahedron"),
+    "three_factor_plane": ((6, 81, 162), "tetrahedron"),
+    "sum_shared_over_launches": ((12, 16, 18), 140),       # 140 stored rows: three launches
+    "sum_shared_one_launch": ((48, 20, 24), 30),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_tile_plans(name):
+    import torch
+    from paper_1505_07690_amd import os3d
+    shape, kind = SHAPES[name]
+    n = _random_orients(kind, 77) if isinstance(kind, int) else inputs.platonic_orientations(kind)
+    p = O.WaveletParams(L=5, s_theta=inputs.s_theta_for(len(n)))
+    vol = inputs.tubes(shape, 2, 1.2, 0.1, 0, 61)
+    ob = O.build_bank(shape, n, p)
+    gb = os3d.Bank(shape, n, p)
+    f = torch.from_numpy(vol).cuda()
+    U, _ = os3d.forward(f, gb)
+    Uo = O.forward(vol.astype(np.float64), ob)
+    assert rel(U.cpu().numpy(), Uo) < TOL
+    rng = np.random.default_rng(5)
+    Un = (rng.standard_normal(Uo.shape) + 1j * rng.standard_normal(Uo.shape)).astype(np.complex64)
+    Ut = torch.from_numpy(Un).cuda()
+    assert rel(os3d.reconstruct(Ut, gb).cpu().numpy(), O.reconstruct(Un.astype(np.complex128), ob)) < TOL
+    assert rel(os3d.adjoint(Ut, gb).cpu().numpy(), O.adjoint(Un.astype(np.complex128), ob)) < TOL
+    gp = os3d.process(f, gb, "identity").cpu().numpy()
+    assert rel(gp, O.reconstruct(Uo, ob)) < TOL
+    for fmt, bound in (("bf16", 4e-3), ("fp16", 5e-4)):
+        Uq, sc = os3d.forward(f, gb, dtype=fmt)
+        Ud = os3d.unpack16(Uq, sc, fmt).cpu().numpy()
+        assert rel(Ud, Uo) < bound
+        rq = os3d.reconstruct(Uq, gb, scales=sc, dtype=fmt).cpu().numpy()
+        assert rel(rq, O.reconstruct(Ud.astype(np.complex128), ob)) < TOL
