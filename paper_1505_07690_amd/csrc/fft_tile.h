@@ -66,8 +66,9 @@ struct TileArgs {
   // plane and row kernels
   int rows, P, A;      // rows = P A rows of x.N values per tile
   int RS, pad;         // LDS row stride; values skipped after every x.R[last]
-  unsigned mrows, mNx, mRL, mP, mA;
+  unsigned mrows, mNx, mRL, mP, mA, mnf;
   long long tiles;     // tiles per volume
+  long long nlines;    // x lines per volume
 };
 
 // ---------------------------------------------------------------- device helpers

@@ -2,19 +2,20 @@
 // fft_tile.h).  A tile is a run of rows of Nx consecutive values: one or
 // more whole (y, x) planes, transformed along both axes while they sit in
 // LDS (one round trip of the intermediate instead of two), or, for planes
-// larger than LDS, rows transformed along x alone.
+// larger than LDS, rows transformed along x alone.  On the way to the
+// spectrum x goes before y, on the way back y before x.
 //
-// The tile is loaded linearly (fully coalesced) with the fused load of the
-// pass; the x stages run with consecutive lanes on consecutive rows (the row
-// stride is odd, so a wave's accesses fall on distinct banks and its
-// twiddles are broadcasts), the y stages with consecutive lanes on
-// consecutive x.  The rows end digit-reversed: the last y stage (or the
-// store loop) reads them in natural order through a table and stores straight
-// to memory with consecutive lanes on consecutive x; an odd last x factor, or
-// one value of padding after every even one, keeps those reads off each
-// other's banks.  Workgroups loop over (pair, tile) tasks and issue the next
-// task's loads before transforming the current one, except complex64 score
-// pairs, whose two members do not fit the registers beside the transform.
+// The first stage of the first axis loads its butterflies straight from
+// memory (the fused load of the pass) and the last stage of the last axis
+// stores straight to memory (the fused store); the stages in between run in
+// place in LDS.  Memory accesses and the y stages take consecutive lanes on
+// consecutive x (an x stage's accesses to memory are runs of N / R values, 64
+// bytes and more); the x stages in LDS take consecutive lanes on consecutive
+// rows: the row stride is odd, so a wave's accesses fall on distinct banks and
+// its twiddles are broadcasts.  The passes are bound by the latency of that
+// chain, not by arithmetic, so a butterfly keeps few registers (no tile in
+// flight) and two or more workgroups share a CU where LDS allows; a workgroup
+// loops over (pair, tile) tasks to keep its tables.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,11 +46,11 @@ struct TileLds {
   u16* xs;  // frequency kx -> position in the row after the DIF
   u16* fx;  // frequency at a DIF position (without padding)
   u16* fy;
-  u16* ys;  // SEQ: frequency ky -> row after the DIF
+  u16* ys;  // frequency ky -> row after the DIF
 };
 
 // conj: the twiddles of the inverse direction
-template <bool PLANE, bool SEQ>
+template <bool PLANE>
 __device__ __forceinline__ TileLds tile_lds(const TileArgs& a, float2* lds, bool conj) {
   TileLds t;
   t.buf = lds;
@@ -69,19 +70,76 @@ __device__ __forceinline__ TileLds tile_lds(const TileArgs& a, float2* lds, bool
   }
   if constexpr (PLANE) {
     for (int i = threadIdx.x; i < a.y.N; i += blockDim.x) {
-      const int f = freq_of(a.y, i);
       t.twy[i] = conj ? cconj(a.y.tw[i]) : a.y.tw[i];
+      const int f = freq_of(a.y, i);
       t.fy[i] = (u16)f;
-      if constexpr (SEQ) t.ys[f] = (u16)i;
+      t.ys[f] = (u16)i;
     }
   }
   __syncthreads();
   return t;
 }
 
-// Stage i of the rows, in place.
-template <bool SEQ, bool INV, bool DIT, bool REAL = false>
-__device__ __forceinline__ void x_stage(const TileArgs& a, const TileLds& t, int i) {
+// R values of one thread at g + r d of pair j
+template <int LM, int DT, int R>
+__device__ __forceinline__ void tile_load(const PassArgs& p, int j, long long g, long long d, float2* v) {
+  if constexpr (LM == LM_REAL) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = make_float2(ldnt(p.src_r + g + r * d), 0.f);
+  } else if constexpr (LM == LM_C) {
+    const float2* s = p.src_c + j * p.src_stride + g;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = ldnt(s + r * d);
+  } else {
+    using Word = typename std::conditional<DT == OS3D_C64, float2, unsigned int>::type;
+    const int ia = p.oa[j], ib = p.ob[j];
+    auto value = [](Word w, float sc) -> float2 {
+      if constexpr (DT == OS3D_C64) return w;
+      else return score_value<DT>(w, sc);
+    };
+    const float sa = DT == OS3D_C64 ? 1.f : p.scales[ia];
+    const Word* ua = (const Word*)p.U + (long long)ia * p.V + g;
+    Word wa[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) wa[r] = ldnt(ua + r * d);
+    if (ib >= 0) {
+      const float sb = DT == OS3D_C64 ? 1.f : p.scales[ib];
+      const Word* ub = (const Word*)p.U + (long long)ib * p.V + g;
+      Word wb[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) wb[r] = ldnt(ub + r * d);
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = cadd(value(wa[r], sa), cconj(value(wb[r], sb)));
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = value(wa[r], sa);
+    }
+  }
+}
+
+// The transformed values of a butterfly, slot r at frequency seq_slot(r), stored at g + k d
+template <int SM, int DT, int R, int RB>
+__device__ __forceinline__ void tile_store(const PassArgs& p, int j, long long g, long long d, const float2* v) {
+  float2 u[R], dummy[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) u[seq_slot<R, RB>(r)] = v[r];
+  store_k<SM, DT, R>(p, j, g, d, u, dummy);
+}
+
+template <bool SEQ, bool INV, bool DIT, int R, int RB, bool REAL = false>
+__device__ __forceinline__ void butterfly(const AxisT& x, int i, const float2* tw, int t, float2* v, float sgn) {
+  if constexpr (SEQ) {
+    seq_butterfly<R, RB, REAL>(v, tw, t, x.S[i], x.tstep[i], i == 0, sgn);
+  } else {
+    if (DIT ? i < x.nst - 1 : i > 0) twiddle<R, INV>(v, tw, DIT ? t * x.tstep[i] : t * x.S[i]);
+    dft_r<R>(v, INV ? 1.f : -1.f);
+  }
+}
+
+// Stage i of the rows in LDS, in place; phi: between the last stage of the
+// inverse DFT and the first of the forward one.
+template <bool SEQ, bool INV, bool DIT, bool PHI = false>
+__device__ __forceinline__ void x_stage(const TileArgs& a, const TileLds& t, int i, int j = 0) {
   const AxisT& x = a.x;
   const int S = x.S[i];
   const bool last = i == x.nst - 1;
@@ -97,11 +155,11 @@ __device__ __forceinline__ void x_stage(const TileArgs& a, const TileLds& t, int
       float2 v[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) v[r] = q[r * Sp];
-      if constexpr (SEQ) {
-        seq_butterfly<R, RB, REAL>(v, t.twx, t.fx[u * R * S], S, x.tstep[i], i == 0, a.p.sgn);
-      } else {
-        if (DIT ? !last : i > 0) twiddle<R, INV>(v, t.twx, DIT ? l * x.tstep[i] : t.fx[u * R * S] * S);
-        dft_r<R>(v, INV ? 1.f : -1.f);
+      butterfly<SEQ, INV, DIT, R, RB>(x, i, t.twx, DIT ? l : t.fx[u * R * S], v, a.p.sgn);
+      if constexpr (PHI) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = phi_apply(a.p, j, v[r]);
+        dft_r<R>(v, -1.f);
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) q[r * Sp] = v[r];
@@ -109,7 +167,51 @@ __device__ __forceinline__ void x_stage(const TileArgs& a, const TileLds& t, int
   });
 }
 
-// Stage i of the columns: fn(R, RB, v, q, d, pos, col, plane) takes the
+// First stage of the rows, from memory.
+template <int LM, int DT, bool SEQ, bool INV, class Done>
+__device__ __forceinline__ void x_first(const TileArgs& a, const TileLds& t, int j, long long g0, int nrows,
+                                        Done done) {
+  const AxisT& x = a.x;
+  const int S = x.S[0], Sp = x.nst == 1 ? 1 : S + fdiv(S, a.mRL) * a.pad;
+  with_stage<SEQ>(x, 0, OS3D_SEQ_FN(rc, rb) {
+    constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
+    const int total = nrows * S;
+    for (int id = threadIdx.x; id < total; id += blockDim.x) {
+      const int row = fdiv(id, x.mS[0]), l = id - row * S;
+      float2 v[R];
+      tile_load<LM, DT, R>(a.p, j, g0 + row * x.N + l, S, v);
+      butterfly<SEQ, INV, false, R, RB, LM == LM_REAL>(x, 0, t.twx, 0, v, a.p.sgn);
+      done(rc, rb, v, t.buf + row * a.RS + t.xl[l], Sp, row);
+    }
+  });
+}
+
+// Last stage of the rows, to memory (PLANE: the rows are digit-reversed).
+template <int SM, int DT, bool PLANE, bool SEQ, bool INV>
+__device__ __forceinline__ void x_last(const TileArgs& a, const TileLds& t, int j, long long g0, int nrows) {
+  const AxisT& x = a.x;
+  const int i = x.nst - 1;
+  with_stage<SEQ>(x, i, OS3D_SEQ_FN(rc, rb) {
+    constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
+    const int nf = x.nb[i], total = nrows * nf;
+    for (int id = threadIdx.x; id < total; id += blockDim.x) {
+      const int row = fdiv(id, a.mnf), f = id - row * nf;  // lowest frequency of the butterfly
+      int lrow = row;
+      if constexpr (PLANE) {
+        const int plane = fdiv(row, a.mA);
+        lrow = plane * a.A + t.ys[row - plane * a.A];
+      }
+      const float2* q = t.buf + lrow * a.RS + t.xs[f];
+      float2 v[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = q[r];
+      butterfly<SEQ, INV, false, R, RB>(x, i, t.twx, f, v, a.p.sgn);
+      tile_store<SM, DT, R, RB>(a.p, j, g0 + row * x.N + f, nf, v);
+    }
+  });
+}
+
+// Stage i of the columns in LDS: fn(R, RB, v, q, d, pos, col, plane) takes the
 // transformed butterfly at row position pos of column col (LDS address q,
 // stride d).  Columns go by position in the row (xl), or in the order of
 // their frequencies (NATURAL).
@@ -117,167 +219,118 @@ template <bool SEQ, bool INV, bool DIT, bool NATURAL, class Fn>
 __device__ __forceinline__ void y_stage(const TileArgs& a, const TileLds& t, int i, Fn fn) {
   const AxisT& y = a.y;
   const int S = y.S[i];
-  const bool last = i == y.nst - 1;
   with_stage<SEQ>(y, i, OS3D_SEQ_FN(rc, rb) {
     constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
     const int total = a.P * y.nb[i] * a.x.N;
     for (int id = threadIdx.x; id < total; id += blockDim.x) {
       const int e = fdiv(id, a.mNx), col = id - e * a.x.N;
       const int b = fdiv(e, a.mP), plane = e - b * a.P;
-      const int u = fdiv(b, y.mS[i]), l = b - u * S;
-      float2* q = t.buf + (plane * a.A + u * R * S + l) * a.RS + (NATURAL ? t.xs : t.xl)[col];
+      const int u = fdiv(b, y.mS[i]), l = b - u * S, pos = u * R * S + l;
+      float2* q = t.buf + (plane * a.A + pos) * a.RS + (NATURAL ? t.xs : t.xl)[col];
       const int d = S * a.RS;
       float2 v[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) v[r] = q[r * d];
-      if constexpr (SEQ) {
-        seq_butterfly<R, RB>(v, t.twy, t.fy[u * R * S], S, y.tstep[i], i == 0, a.p.sgn);
-      } else {
-        if (DIT ? !last : i > 0) twiddle<R, INV>(v, t.twy, DIT ? l * y.tstep[i] : t.fy[u * R * S] * S);
-        dft_r<R>(v, INV ? 1.f : -1.f);
-      }
-      fn(rc, rb, v, q, d, u * R * S, col, plane);
+      butterfly<SEQ, INV, DIT, R, RB>(y, i, t.twy, DIT ? l : t.fy[u * R * S], v, a.p.sgn);
+      fn(rc, rb, v, q, d, pos, col, plane);
+    }
+  });
+}
+
+// First stage of the columns, from memory.
+template <int LM, int DT, bool SEQ, bool INV>
+__device__ __forceinline__ void y_first(const TileArgs& a, const TileLds& t, int j, long long g0) {
+  const AxisT& y = a.y;
+  const int S = y.S[0];
+  with_stage<SEQ>(y, 0, OS3D_SEQ_FN(rc, rb) {
+    constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
+    const int total = a.P * S * a.x.N;
+    for (int id = threadIdx.x; id < total; id += blockDim.x) {
+      const int e = fdiv(id, a.mNx), col = id - e * a.x.N;
+      const int b = fdiv(e, a.mP), row = (e - b * a.P) * a.A + b;
+      float2 v[R];
+      tile_load<LM, DT, R>(a.p, j, g0 + row * a.x.N + col, (long long)S * a.x.N, v);
+      butterfly<SEQ, INV, false, R, RB>(y, 0, t.twy, 0, v, a.p.sgn);
+      float2* q = t.buf + row * a.RS + t.xl[col];
+      const int d = S * a.RS;
+#pragma unroll
+      for (int r = 0; r < R; ++r) q[r * d] = v[r];
     }
   });
 }
 
 struct KeepInLds {
+  // columns
   template <class RC, class RB>
   __device__ __forceinline__ void operator()(RC, RB, const float2* v, float2* q, int d, int, int, int) const {
 #pragma unroll
     for (int r = 0; r < RC::value; ++r) q[r * d] = v[r];
   }
-};
-
-// The thread's values tid + i T of a tile: raw loads, converted when they are used.
-template <int LM, int DT, int VPT>
-struct TileIn {
-  static constexpr bool kPair = LM == LM_UIN;
-  static constexpr bool kPrefetch = !(LM == LM_UIN && DT == OS3D_C64);
-  using Word = typename std::conditional<LM == LM_REAL, float,
-                                         typename std::conditional<kPair && DT != OS3D_C64, unsigned int,
-                                                                   float2>::type>::type;
-  Word r[VPT], s[kPair ? VPT : 1];
-  bool both;
-  float sa, sb;
-
-  // n values of the tile at g0 of pair j; only the first nval exist
-  __device__ __forceinline__ void issue(const PassArgs& p, int j, long long g0, int n, int nval) {
-    const Word *wr, *ws = nullptr;
-    both = false;
-    if constexpr (LM == LM_REAL) {
-      wr = p.src_r + g0;
-    } else if constexpr (LM == LM_C) {
-      wr = p.src_c + j * p.src_stride + g0;
-    } else {
-      const int ia = p.oa[j], ib = p.ob[j];
-      both = ib >= 0;
-      wr = (const Word*)p.U + (long long)ia * p.V + g0;
-      ws = (const Word*)p.U + (long long)(both ? ib : ia) * p.V + g0;
-      if constexpr (DT != OS3D_C64) {
-        sa = p.scales[ia];
-        sb = both ? p.scales[ib] : 0.f;
-      }
-    }
-    const int T = blockDim.x;
+  // rows
+  template <class RC, class RB>
+  __device__ __forceinline__ void operator()(RC, RB, const float2* v, float2* q, int d, int) const {
 #pragma unroll
-    for (int i = 0; i < VPT; ++i)
-      if (i * T < n) r[i] = ldnt(wr + min((int)threadIdx.x + i * T, nval - 1));
-    if constexpr (kPair) {
-      if (both) {
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-          if (i * T < n) s[i] = ldnt(ws + min((int)threadIdx.x + i * T, nval - 1));
-      }
-    }
-  }
-  __device__ __forceinline__ static float2 val(Word w, float sc) {
-    if constexpr (LM == LM_REAL) return make_float2(w, 0.f);
-    else if constexpr (kPair && DT != OS3D_C64) return score_value<DT>(w, sc);
-    else return w;
-  }
-  __device__ __forceinline__ void put(const TileArgs& a, const TileLds& t, int n) const {
-    const int T = blockDim.x;
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-      const int e = threadIdx.x + i * T;
-      if (e < n) {
-        float2 v = val(r[i], sa);
-        if constexpr (kPair) {
-          if (both) v = cadd(v, cconj(val(s[i], sb)));
-        }
-        const int row = fdiv(e, a.mNx), x = e - row * a.x.N;
-        t.buf[row * a.RS + t.xl[x]] = v;
-      }
-    }
+    for (int r = 0; r < RC::value; ++r) q[r * d] = v[r];
   }
 };
 
-// SEQ: the sequential order of the forward transform into 16-bit scores (x
-// before y on the way to the spectrum, y before x on the way back).
-template <int LM, int SM, int DT, bool PLANE, bool SEQ, int VPT>
+// SEQ: the sequential order of the forward transform into 16-bit scores.
+template <int LM, int SM, int DT, bool PLANE, bool SEQ>
 __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
   constexpr bool INV = SM == SM_UOUT || SM == SM_REAL;  // the other stores end a forward DFT
-  constexpr bool kYFirst = PLANE && SEQ && INV;
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
-  const TileLds t = tile_lds<PLANE, SEQ>(a, lds, SEQ && INV);
-  const int n = a.rows * a.x.N;
+  const TileLds t = tile_lds<PLANE>(a, lds, SEQ && INV);
+  const int n = a.rows * a.x.N, lx = a.x.nst - 1, ly = a.y.nst - 1;
   const long long ntask = a.tiles * p.nb;
-  using In = TileIn<LM, DT, VPT>;
-  In in;
-  auto issue = [&](long long task) {
+  for (long long task = blockIdx.x; task < ntask; task += gridDim.x) {
     const int j = (int)(task / a.tiles);
-    const long long g0 = (task - j * a.tiles) * n;
-    in.issue(p, j, g0, n, (int)min((long long)n, p.V - g0));
-  };
-  long long task = blockIdx.x;
-  if (In::kPrefetch) issue(task);
-  for (; task < ntask; task += gridDim.x) {
-    const int j = (int)(task / a.tiles);
-    const long long g0 = (task - j * a.tiles) * n;
-    if (!In::kPrefetch) issue(task);
-    in.put(a, t, n);
-    if (In::kPrefetch && task + gridDim.x < ntask) issue(task + gridDim.x);
-    __syncthreads();
-    if constexpr (kYFirst) {
-      for (int i = 0; i < a.y.nst; ++i) {
+    const long long tile = task - j * a.tiles, g0 = tile * n;
+    if constexpr (!PLANE) {
+      const int nrows = (int)min((long long)a.rows, a.nlines - tile * a.rows);
+      if (lx == 0) {
+        x_first<LM, DT, SEQ, INV>(a, t, j, g0, nrows,
+                                  [&](auto rc, auto rb, const float2* v, float2*, int, int row) {
+          tile_store<SM, DT, decltype(rc)::value, decltype(rb)::value>(p, j, g0 + row * a.x.N, 1, v);
+        });
+      } else {
+        x_first<LM, DT, SEQ, INV>(a, t, j, g0, nrows, KeepInLds{});
+        __syncthreads();
+        for (int i = 1; i < lx; ++i) {
+          x_stage<SEQ, INV, false>(a, t, i);
+          __syncthreads();
+        }
+        x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, g0, nrows);
+      }
+    } else if constexpr (INV) {
+      y_first<LM, DT, SEQ, INV>(a, t, j, g0);
+      __syncthreads();
+      for (int i = 1; i <= ly; ++i) {
         y_stage<SEQ, INV, false, false>(a, t, i, KeepInLds{});
         __syncthreads();
       }
-    }
-    for (int i = 0; i < a.x.nst; ++i) {
-      x_stage<SEQ, INV, false, LM == LM_REAL>(a, t, i);
+      for (int i = 0; i < lx; ++i) {
+        x_stage<SEQ, INV, false>(a, t, i);
+        __syncthreads();
+      }
+      x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, g0, a.rows);
+    } else {
+      x_first<LM, DT, SEQ, INV>(a, t, j, g0, a.rows, KeepInLds{});
       __syncthreads();
-    }
-    if constexpr (PLANE && !kYFirst) {
-      const int last = a.y.nst - 1;
-      for (int i = 0; i < last; ++i) {
+      for (int i = 1; i <= lx; ++i) {
+        x_stage<SEQ, INV, false>(a, t, i);
+        __syncthreads();
+      }
+      for (int i = 0; i < ly; ++i) {
         y_stage<SEQ, INV, false, false>(a, t, i, KeepInLds{});
         __syncthreads();
       }
       y_stage<SEQ, INV, false, true>(
-          a, t, last, [&](auto rc, auto rb, const float2* v, float2*, int, int pos, int col, int plane) {
+          a, t, ly, [&](auto rc, auto rb, const float2* v, float2*, int, int pos, int col, int plane) {
             constexpr int R = decltype(rc)::value, RB = decltype(rb)::value;
-            const long long g = g0 + (plane * a.A + t.fy[pos]) * a.x.N + col, dn = (long long)(a.A / R) * a.x.N;
-            float2 u[R], dummy[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) u[seq_slot<R, RB>(r)] = v[r];
-            store_k<SM, DT, R>(p, j, g, dn, u, dummy);
+            tile_store<SM, DT, R, RB>(p, j, g0 + (plane * a.A + t.fy[pos]) * a.x.N + col,
+                                      (long long)(a.A / R) * a.x.N, v);
           });
-    } else {
-      // row by row in natural order
-      const int nval = (int)min((long long)n, p.V - g0);
-      for (int e = threadIdx.x; e < nval; e += blockDim.x) {
-        const int row = fdiv(e, a.mNx), x = e - row * a.x.N;
-        int lrow = row;
-        if constexpr (kYFirst) {
-          const int plane = fdiv(row, a.mA);
-          lrow = plane * a.A + t.ys[row - plane * a.A];
-        }
-        float2 u[1] = {t.buf[lrow * a.RS + t.xs[x]]}, dummy[1];
-        store_k<SM, DT, 1>(p, j, g0 + e, 0, u, dummy);
-      }
     }
     __syncthreads();  // the tile is rewritten by the next task
   }
@@ -287,70 +340,59 @@ __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
 // DFT of the tile, Phi on the scores, forward DFT.  The scores stay in
 // digit-reversed order in between (DIF, Phi in the registers of its last
 // stage, DIT).
-template <bool PLANE, int VPT>
+template <bool PLANE>
 __global__ __launch_bounds__(1024) void k_tile_phi(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
-  const TileLds t = tile_lds<PLANE, false>(a, lds, false);
-  const int n = a.rows * a.x.N;
+  const TileLds t = tile_lds<PLANE>(a, lds, false);
+  const int n = a.rows * a.x.N, lx = a.x.nst - 1, ly = a.y.nst - 1;
   const long long ntask = a.tiles * p.nb;
-  using In = TileIn<LM_C, OS3D_C64, VPT>;
-  In in;
-  auto issue = [&](long long task) {
+  for (long long task = blockIdx.x; task < ntask; task += gridDim.x) {
     const int j = (int)(task / a.tiles);
-    const long long g0 = (task - j * a.tiles) * n;
-    in.issue(p, j, g0, n, (int)min((long long)n, p.V - g0));
-  };
-  long long task = blockIdx.x;
-  issue(task);
-  const int lx = a.x.nst - 1;
-  for (; task < ntask; task += gridDim.x) {
-    const int j = (int)(task / a.tiles);
-    const long long g0 = (task - j * a.tiles) * n;
-    in.put(a, t, n);
-    if (task + gridDim.x < ntask) issue(task + gridDim.x);
-    __syncthreads();
-    for (int i = 0; i <= lx; ++i) {
-      x_stage<false, true, false>(a, t, i);
-      __syncthreads();
-    }
+    const long long tile = task - j * a.tiles, g0 = tile * n;
+    const int nrows = PLANE ? a.rows : (int)min((long long)a.rows, a.nlines - tile * a.rows);
     if constexpr (PLANE) {
-      const int ly = a.y.nst - 1;
-      for (int i = 0; i < ly; ++i) {
+      y_first<LM_C, OS3D_C64, false, true>(a, t, j, g0);
+      __syncthreads();
+      for (int i = 1; i <= ly; ++i) {
         y_stage<false, true, false, false>(a, t, i, KeepInLds{});
         __syncthreads();
       }
-      y_stage<false, true, false, false>(a, t, ly, [&](auto rc, auto, const float2* v, float2* q, int d, int, int, int) {
-        constexpr int R = decltype(rc)::value;
-        float2 u[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) u[r] = phi_apply(p, j, v[r]);
-        dft_r<R>(u, -1.f);
-#pragma unroll
-        for (int r = 0; r < R; ++r) q[r * d] = u[r];
-      });
-      __syncthreads();
-      for (int i = ly - 1; i >= 0; --i) {
-        y_stage<false, false, true, false>(a, t, i, KeepInLds{});
-        __syncthreads();
-      }
     } else {
-      for (int e = threadIdx.x; e < n; e += blockDim.x) {
+      for (int e = threadIdx.x; e < nrows * a.x.N; e += blockDim.x) {
         const int row = fdiv(e, a.mNx), x = e - row * a.x.N;
-        float2* q = t.buf + row * a.RS + t.xl[x];
-        *q = phi_apply(p, j, *q);
+        t.buf[row * a.RS + t.xl[x]] = p.src_c[j * p.src_stride + g0 + e];
       }
       __syncthreads();
     }
-    for (int i = lx; i >= 0; --i) {
+    for (int i = 0; i < lx; ++i) {
+      x_stage<false, true, false>(a, t, i);
+      __syncthreads();
+    }
+    x_stage<false, true, false, true>(a, t, lx, j);
+    __syncthreads();
+    for (int i = lx - 1; i >= 0; --i) {
       x_stage<false, false, true>(a, t, i);
       __syncthreads();
     }
-    const int nval = (int)min((long long)n, p.V - g0);
     float2* dst = p.dst_c + j * p.dst_stride + g0;
-    for (int e = threadIdx.x; e < nval; e += blockDim.x) {
-      const int row = fdiv(e, a.mNx), x = e - row * a.x.N;
-      dst[e] = t.buf[row * a.RS + t.xl[x]];
+    if constexpr (PLANE) {
+      for (int i = ly; i > 0; --i) {
+        y_stage<false, false, true, false>(a, t, i, KeepInLds{});
+        __syncthreads();
+      }
+      y_stage<false, false, true, false>(
+          a, t, 0, [&](auto rc, auto, const float2* v, float2*, int, int pos, int col, int plane) {
+            constexpr int R = decltype(rc)::value;
+            const int o = (plane * a.A + pos) * a.x.N + col, d = (a.A / R) * a.x.N;
+#pragma unroll
+            for (int r = 0; r < R; ++r) dst[o + r * d] = v[r];
+          });
+    } else {
+      for (int e = threadIdx.x; e < nrows * a.x.N; e += blockDim.x) {
+        const int row = fdiv(e, a.mNx), x = e - row * a.x.N;
+        dst[e] = t.buf[row * a.RS + t.xl[x]];
+      }
     }
     __syncthreads();
   }
@@ -358,7 +400,8 @@ __global__ __launch_bounds__(1024) void k_tile_phi(TileArgs a) {
 
 // ---------------------------------------------------------------- host side
 constexpr size_t kLdsBytes = 160 * 1024;
-constexpr int kMaxVpt = 20;  // values per thread and task
+
+constexpr int kMaxPlane = 20 * 1024;  // values of a plane in LDS
 
 struct TilePlan {
   int threads, wgs;  // per workgroup; workgroups per CU
@@ -377,7 +420,7 @@ static size_t tile_bytes(int rows, int RS, int Nx, int Ny) {
 }
 
 bool plane_fits(int Ny, int Nx) {
-  if ((long long)Ny * Nx > kMaxVpt * 1024) return false;
+  if ((long long)Ny * Nx > kMaxPlane) return false;
   int pad;
   const int RS = std::max(row_stride(make_axis(Nx, nullptr, true), pad), row_stride(make_axis_seq(Nx, nullptr), pad));
   return tile_bytes(Ny, RS, Nx, Ny) <= kLdsBytes;
@@ -402,7 +445,8 @@ static TileArgs tile_args(const os3d_bank* b, const PassArgs& p, bool plane, boo
   } else {
     a.P = 1;
     a.A = a.rows = std::max(1, std::min(64, 6144 / Nx));
-    a.tiles = ((long long)Nz * Ny + a.rows - 1) / a.rows;
+    a.nlines = (long long)Nz * Ny;
+    a.tiles = (a.nlines + a.rows - 1) / a.rows;
   }
   a.mrows = fdiv_mul((unsigned)a.rows);
   a.mNx = fdiv_mul((unsigned)Nx);
@@ -410,12 +454,12 @@ static TileArgs tile_args(const os3d_bank* b, const PassArgs& p, bool plane, boo
   a.mP = fdiv_mul((unsigned)a.P);
   a.mA = fdiv_mul((unsigned)a.A);
   q.lds = tile_bytes(a.rows, a.RS, Nx, plane ? Ny : 0);
-  // eight values per thread; a workgroup that shares its CU takes up to 512 threads
+  a.mnf = fdiv_mul((unsigned)a.x.nb[a.x.nst - 1]);
+  // a butterfly of ten values or so per thread; a workgroup that shares its CU takes up to 512 threads
   const int n = a.rows * Nx;
   const int cap = 2 * q.lds <= kLdsBytes ? 512 : 1024;
-  q.threads = std::min(cap, (n + 511) / 512 * 64);
-  if ((n + q.threads - 1) / q.threads > kMaxVpt) q.threads = 1024;
-  q.wgs = (int)std::max<size_t>(1, std::min<size_t>(kLdsBytes / q.lds, 1024 / q.threads));
+  q.threads = std::min(cap, (n + 639) / 640 * 64);
+  q.wgs = (int)std::max<size_t>(1, std::min<size_t>(kLdsBytes / q.lds, 1280 / q.threads));  // five waves per SIMD
   return a;
 }
 
@@ -450,27 +494,20 @@ static int launch_tiles(K kernel, const TilePlan& q, const TileArgs& a, hipStrea
   return OS3D_OK;
 }
 
-template <int LM, int SM, int DT, bool PLANE, bool SEQ>
-static int launch_tile_dt(const TilePlan& q, const TileArgs& a, hipStream_t st) {
-  const int n = a.rows * a.x.N;
-  if (n <= 8 * q.threads) return launch_tiles(k_tile<LM, SM, DT, PLANE, SEQ, 8>, q, a, st);
-  return launch_tiles(k_tile<LM, SM, DT, PLANE, SEQ, kMaxVpt>, q, a, st);
-}
-
 template <int LM, int SM, bool PLANE>
 static int launch_tile_p(const TilePlan& q, const TileArgs& a, bool seq, hipStream_t st) {
   if constexpr (SM == SM_UOUT) {
-    if (a.p.dtype == OS3D_BF16X2) return launch_tile_dt<LM, SM, OS3D_BF16X2, PLANE, true>(q, a, st);
-    if (a.p.dtype == OS3D_F16X2) return launch_tile_dt<LM, SM, OS3D_F16X2, PLANE, true>(q, a, st);
+    if (a.p.dtype == OS3D_BF16X2) return launch_tiles(k_tile<LM, SM, OS3D_BF16X2, PLANE, true>, q, a, st);
+    if (a.p.dtype == OS3D_F16X2) return launch_tiles(k_tile<LM, SM, OS3D_F16X2, PLANE, true>, q, a, st);
   }
   if constexpr (LM == LM_UIN) {
-    if (a.p.dtype == OS3D_BF16X2) return launch_tile_dt<LM, SM, OS3D_BF16X2, PLANE, false>(q, a, st);
-    if (a.p.dtype == OS3D_F16X2) return launch_tile_dt<LM, SM, OS3D_F16X2, PLANE, false>(q, a, st);
+    if (a.p.dtype == OS3D_BF16X2) return launch_tiles(k_tile<LM, SM, OS3D_BF16X2, PLANE, false>, q, a, st);
+    if (a.p.dtype == OS3D_F16X2) return launch_tiles(k_tile<LM, SM, OS3D_F16X2, PLANE, false>, q, a, st);
   }
   if constexpr (LM == LM_REAL) {
-    if (seq) return launch_tile_dt<LM, SM, OS3D_C64, PLANE, true>(q, a, st);
+    if (seq) return launch_tiles(k_tile<LM, SM, OS3D_C64, PLANE, true>, q, a, st);
   }
-  return launch_tile_dt<LM, SM, OS3D_C64, PLANE, false>(q, a, st);
+  return launch_tiles(k_tile<LM, SM, OS3D_C64, PLANE, false>, q, a, st);
 }
 
 template <int LM, int SM>
@@ -483,10 +520,7 @@ int launch_tile(const os3d_bank* b, const PassArgs& p, bool plane, bool seq, hip
 int launch_tile_phi(const os3d_bank* b, const PassArgs& p, bool plane, hipStream_t st) {
   TilePlan q;
   const TileArgs a = tile_args(b, p, plane, false, q);
-  const bool few = a.rows * a.x.N <= 8 * q.threads;
-  if (plane)
-    return few ? launch_tiles(k_tile_phi<true, 8>, q, a, st) : launch_tiles(k_tile_phi<true, kMaxVpt>, q, a, st);
-  return few ? launch_tiles(k_tile_phi<false, 8>, q, a, st) : launch_tiles(k_tile_phi<false, kMaxVpt>, q, a, st);
+  return plane ? launch_tiles(k_tile_phi<true>, q, a, st) : launch_tiles(k_tile_phi<false>, q, a, st);
 }
 
 template int launch_tile<LM_REAL, SM_C>(const os3d_bank*, const PassArgs&, bool, bool, hipStream_t);
