@@ -48,6 +48,7 @@ struct AxisT {
   int tstep[kMaxStages];        // N / (R S): the product of the factors before the stage
   unsigned mS[kMaxStages];      // fast division by S
   int nf, F[kMaxFactors];       // single factors
+  unsigned mF[kMaxFactors];
   const float2* tw;             // exp(-2 pi i j / N)
 };
 
@@ -109,7 +110,7 @@ __device__ __forceinline__ void twiddle(float2* v, const float2* tw, int idx) {
 __device__ __forceinline__ int freq_of(const AxisT& ax, int p) {
   int f = 0;
   for (int i = ax.nf - 1; i >= 0; --i) {
-    const int q = p / ax.F[i];
+    const int q = fdiv(p, ax.mF[i]);
     f = (p - q * ax.F[i]) + ax.F[i] * f;
     p = q;
   }
@@ -324,6 +325,7 @@ inline void set_stages(AxisT& a, int N, const float* tw) {
     a.tstep[i] = N / (a.R[i] * S);
     a.mS[i] = fdiv_mul((unsigned)S);
   }
+  for (int i = 0; i < a.nf; ++i) a.mF[i] = fdiv_mul((unsigned)a.F[i]);
   a.tw = (const float2*)tw;
 }
 

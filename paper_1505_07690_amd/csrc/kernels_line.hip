@@ -310,7 +310,9 @@ __global__ __launch_bounds__(1024) void k_line_div(TileArgs a) {
   divide_inverse(a, t, x, col, valid);
 }
 
-// DFT of the y lines of every pair's volume, in place or from src to dst.
+// DFT of the y lines of every pair's volume, in place or from src to dst (one
+// tile per workgroup: taking the lines of several pairs through one workgroup
+// measured slower, 780 -> 910 us at 180 x 240 x 216 x 21 pairs).
 template <bool INV, int RL>
 __global__ __launch_bounds__(1024) void k_line_y(TileArgs a) {
   extern __shared__ float2 lds[];
@@ -511,6 +513,9 @@ static int check_line(const char* what) {
 struct LinePlan {
   int lw, threads;
   size_t lds;
+  // workgroups that keep the chip busy: eight waves per CU (64^3 x 21 pairs: 95
+  // us a job, 97 with thirty-two; 96 x 80 x 64 x 81: 708 and 724)
+  long long fill() const { return 256LL * 512 / threads; }
 };
 
 template <class K>
@@ -521,8 +526,10 @@ static void launch_line(K kernel, dim3 grid, const LinePlan& q, const TileArgs& 
 
 // Lines per workgroup: as many as fill 512 threads with one butterfly each
 // (up to 64 KB of tile, two workgroups per CU), at least runs of 16 values
-// where 1024 threads allow; fewer (down to 16) while the grid is smaller than
-// two workgroups per CU.
+// where 1024 threads allow; down to runs of 32 values while the grid is smaller
+// than two workgroups per CU.  Shorter runs cost more than the idle CUs they
+// fill: at 180 x 240 x 216 (21 pairs) runs of 128 bytes instead of 256 take a
+// job from 4.72 to 5.25 ms, at 64^3 from 95 to 103 us.
 static LinePlan line_plan(const AxisT& z, long long lines) {
   int rmin = 16;
   for (int i = 0; i < z.nst; ++i) rmin = std::min(rmin, z.R[i]);
@@ -530,7 +537,7 @@ static LinePlan line_plan(const AxisT& z, long long lines) {
   int lw = 0;
   while (lw < 8 && (2 << lw) * nbf <= 512 && (2 << lw) * z.N <= 8192) ++lw;
   while (lw < 4 && (2 << lw) * nbf <= 1024 && (2 << lw) * z.N <= 8192) ++lw;
-  while (lw > 4 && ((lines + (1 << lw) - 1) >> lw) < 512) --lw;
+  while (lw > 5 && ((lines + (1 << lw) - 1) >> lw) < 512) --lw;
   LinePlan q;
   q.lw = lw;
   q.threads = std::min(1024, ((nbf << lw) + 63) / 64 * 64);
@@ -556,9 +563,13 @@ int zline_tiles(const os3d_bank* b, bool seq) {
   return zline_args(b, PassArgs{}, q, seq).chunks;
 }
 
+// With fewer tiles than fill the chip the pairs of a launch are shared out, at
+// least three to a workgroup (each share costs a volume of partial sums and
+// its read).
 int zline_acc_groups(const os3d_bank* b, int nb) {
-  const int tiles = zline_tiles(b, false);
-  return std::max(1, std::min(std::min(8, nb / 2), 512 / std::max(1, tiles)));
+  LinePlan q;
+  const TileArgs a = zline_args(b, PassArgs{}, q);
+  return (int)std::max(1LL, std::min<long long>(std::min(8, nb / 3), q.fill() / a.chunks));
 }
 
 int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
@@ -567,7 +578,7 @@ int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
   TileArgs a = zline_args(b, p, q, seq);
   // the forward DFT is repeated by every workgroup of a tile: share the
   // pairs only as far as it takes to fill the chip
-  a.groups = std::max(1, std::min(p.nb, (1024 + a.chunks - 1) / a.chunks));
+  a.groups = (int)std::max(1LL, std::min<long long>(p.nb, (q.fill() + a.chunks - 1) / a.chunks));
   const dim3 grid((unsigned)a.chunks, (unsigned)a.groups);
   if (seq)
     with_seq(a.y.R[0], a.y.RB[0], [&](auto rc, auto rb) {
@@ -608,7 +619,8 @@ int launch_yline(const os3d_bank* b, const PassArgs& p, bool seq, hipStream_t st
   const LinePlan q = line_plan(a.y, a.lines);
   a.lw = q.lw;
   a.chunks = (int)((b->dims[2] + (1LL << q.lw) - 1) >> q.lw);
-  const dim3 grid((unsigned)(a.chunks * b->dims[0]), (unsigned)p.nb);
+  const long long tiles = a.chunks * b->dims[0];
+  const dim3 grid((unsigned)tiles, (unsigned)p.nb);
   if (seq) {
     launch_line(k_line_y_seq, grid, q, a, st);
     return check_line("k_line_y_seq");

@@ -2,8 +2,10 @@
 // fft_tile.h).  A tile is a run of rows of Nx consecutive values: one or
 // more whole (y, x) planes, transformed along both axes while they sit in
 // LDS (one round trip of the intermediate instead of two), or, for planes
-// larger than LDS, rows transformed along x alone.  On the way to the
-// spectrum x goes before y, on the way back y before x.
+// larger than LDS, rows transformed along x alone.  y goes before x: the loads
+// are whole rows then, and the shorter runs are the stores' (the pair load of
+// 96 x 80 x 64 x 41 pairs: 108 us, 117 with x first); only the spectrum of a
+// volume whose scores are stored in 16 bits takes x first (its order is fixed).
 //
 // The first stage of the first axis loads its butterflies straight from
 // memory (the fused load of the pass) and the last stage of the last axis
@@ -278,6 +280,7 @@ struct KeepInLds {
 template <int LM, int SM, int DT, bool PLANE, bool SEQ>
 __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
   constexpr bool INV = SM == SM_UOUT || SM == SM_REAL;  // the other stores end a forward DFT
+  constexpr bool kXFirst = SEQ && !INV;
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const TileLds t = tile_lds<PLANE>(a, lds, SEQ && INV);
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
         }
         x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, g0, nrows);
       }
-    } else if constexpr (INV) {
+    } else if constexpr (!kXFirst) {
       y_first<LM, DT, SEQ, INV>(a, t, j, g0);
       __syncthreads();
       for (int i = 1; i <= ly; ++i) {
