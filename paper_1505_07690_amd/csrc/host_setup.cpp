@@ -64,6 +64,7 @@ std::vector<double> geodesic_icosahedron(int freq) {
   const double e2 = 4.0;  // squared edge length of this icosahedron
   auto adj = [&](int i, int j) { return i != j && std::fabs(dist2(i, j) - e2) < 1e-9; };
   std::vector<double> out;
+  out.reserve((size_t)3 * (10 * freq * freq + 2));
   auto emit = [&](double x, double y, double z) {
     double r = std::sqrt(x * x + y * y + z * z);
     out.push_back(x / r);
@@ -92,47 +93,81 @@ std::vector<double> geodesic_icosahedron(int freq) {
   return out;
 }
 
-// Least-squares fit min ||Y c - values|| with Y[p][l] = sqrt((2l+1)/4pi) P_l(z_p),
-// by Householder QR (the pseudo-inverse solution for a full-column-rank Y).
-bool zonal_fit(int L, const std::vector<double>& pts, const std::vector<double>& values, std::vector<double>& c) {
-  const int m = (int)values.size(), n = L + 1;
-  if (m < n) return false;
-  std::vector<double> A((size_t)m * n), b(values);
-  std::vector<double> P(n);
-  for (int p = 0; p < m; ++p) {
-    legendre(L, pts[3 * p + 2], P.data());
-    for (int l = 0; l < n; ++l) A[(size_t)p * n + l] = std::sqrt((2.0 * l + 1.0) / (4.0 * kPi)) * P[l];
-  }
+// Householder QR solution of min ||A c - b||, A column-major m x n.
+static bool solve_least_squares(int m, int n, std::vector<double>& A, std::vector<double>& b, std::vector<double>& c) {
+  // sums of products in four chains (one chain is a dependent addition per row)
+  auto dot = [](const double* x, const double* y, int len) {
+    double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    int i = 0;
+    for (; i + 4 <= len; i += 4) {
+      s0 += x[i] * y[i];
+      s1 += x[i + 1] * y[i + 1];
+      s2 += x[i + 2] * y[i + 2];
+      s3 += x[i + 3] * y[i + 3];
+    }
+    for (; i < len; ++i) s0 += x[i] * y[i];
+    return (s0 + s1) + (s2 + s3);
+  };
+  auto reflect = [&](const double* v, double vnorm2, double* x, int len) {
+    const double s = 2.0 * dot(v, x, len) / vnorm2;
+    for (int i = 0; i < len; ++i) x[i] -= s * v[i];
+  };
   std::vector<double> diag(n);
   for (int j = 0; j < n; ++j) {
-    double norm = 0;
-    for (int i = j; i < m; ++i) norm += A[(size_t)i * n + j] * A[(size_t)i * n + j];
-    norm = std::sqrt(norm);
+    double* v = &A[(size_t)j * m + j];
+    const int len = m - j;
+    const double norm = std::sqrt(dot(v, v, len));
     if (norm == 0.0) return false;
-    double alpha = A[(size_t)j * n + j] > 0 ? -norm : norm;
-    // v = x - alpha e1, stored in column j (rows j..m-1)
-    A[(size_t)j * n + j] -= alpha;
-    double vnorm2 = 0;
-    for (int i = j; i < m; ++i) vnorm2 += A[(size_t)i * n + j] * A[(size_t)i * n + j];
-    for (int k = j + 1; k < n; ++k) {
-      double s = 0;
-      for (int i = j; i < m; ++i) s += A[(size_t)i * n + j] * A[(size_t)i * n + k];
-      s = 2.0 * s / vnorm2;
-      for (int i = j; i < m; ++i) A[(size_t)i * n + k] -= s * A[(size_t)i * n + j];
-    }
-    double s = 0;
-    for (int i = j; i < m; ++i) s += A[(size_t)i * n + j] * b[i];
-    s = 2.0 * s / vnorm2;
-    for (int i = j; i < m; ++i) b[i] -= s * A[(size_t)i * n + j];
+    const double alpha = v[0] > 0 ? -norm : norm;
+    v[0] -= alpha;  // v = x - alpha e1, stored in column j
+    const double vnorm2 = dot(v, v, len);
+    for (int k = j + 1; k < n; ++k) reflect(v, vnorm2, &A[(size_t)k * m + j], len);
+    reflect(v, vnorm2, &b[j], len);
     diag[j] = alpha;
   }
   c.assign(n, 0.0);
   for (int j = n - 1; j >= 0; --j) {
     double s = b[j];
-    for (int k = j + 1; k < n; ++k) s -= A[(size_t)j * n + k] * c[k];
+    for (int k = j + 1; k < n; ++k) s -= A[(size_t)k * m + j] * c[k];
     c[j] = s / diag[j];
   }
   return true;
+}
+
+// Distinct heights z of the points (to 1e-12) and how many points have each.
+// A zonal function depends on z alone, and the geodesic icosahedron of
+// frequency 15 has about a quarter as many heights as points.
+static void point_heights(const std::vector<double>& pts, std::vector<double>& z, std::vector<double>& count) {
+  std::vector<double> all(pts.size() / 3);
+  for (size_t i = 0; i < all.size(); ++i) all[i] = pts[3 * i + 2];
+  std::sort(all.begin(), all.end());
+  z.clear();
+  count.clear();
+  for (double h : all) {
+    if (z.empty() || h - z.back() > 1e-12) {
+      z.push_back(h);
+      count.push_back(0.0);
+    }
+    count.back() += 1.0;
+  }
+}
+
+// Least-squares fit min sum_p count_p (sum_l c_l Y_l0(z_p) - values_p)^2,
+// Y_l0 = sqrt((2l+1)/4pi) P_l, by Householder QR of the rows times
+// sqrt(count): the pseudo-inverse solution over all points (full column rank).
+static bool zonal_fit(int L, const std::vector<double>& z, const std::vector<double>& count,
+                      const std::vector<double>& values, std::vector<double>& c) {
+  const int m = (int)z.size(), n = L + 1;
+  if (m < n) return false;
+  std::vector<double> A((size_t)m * n), b(m), P(n), norm(n);
+  for (int l = 0; l < n; ++l) norm[l] = std::sqrt((2.0 * l + 1.0) / (4.0 * kPi));
+  for (int p = 0; p < m; ++p) {
+    const double w = std::sqrt(count[p]);
+    legendre(L, z[p], P.data());
+    for (int l = 0; l < n; ++l) A[(size_t)l * m + p] = w * norm[l] * P[l];
+    b[p] = w * values[p];
+  }
+  return solve_least_squares(m, n, A, b, c);
 }
 
 // Cake wavelet (Eq. 14): Funk transform c_l -> 2 pi P_l(0) c_l (Eq. 16) for
@@ -210,14 +245,12 @@ void wavelet_coeffs(const os3d_wavelet_params& p, std::vector<double>& c, std::v
   if (p.coeffs == OS3D_COEFFS_QUADRATURE) {
     quadrature_coeffs(p, c);
   } else {
-    std::vector<double> pts = geodesic_icosahedron(15);
-    const int np = (int)pts.size() / 3;
-    std::vector<double> vals(np);
-    for (int i = 0; i < np; ++i) {
-      double z = std::max(-1.0, std::min(1.0, pts[3 * i + 2]));
-      vals[i] = bspline(p.k, std::acos(z) / p.s_theta);
-    }
-    zonal_fit(p.L, pts, vals, c);
+    std::vector<double> z, count;
+    point_heights(geodesic_icosahedron(15), z, count);
+    std::vector<double> vals(z.size());
+    for (size_t i = 0; i < z.size(); ++i)
+      vals[i] = bspline(p.k, std::acos(std::max(-1.0, std::min(1.0, z[i]))) / p.s_theta);
+    zonal_fit(p.L, z, count, vals, c);
   }
   a.assign(p.L + 1, 0.0);
   cake_coeffs(p.L, c.data(), p.variant, a.data());

@@ -89,7 +89,7 @@ static void make_rows(const double* o, int n, std::vector<int>& partner, std::ve
 }
 
 struct BankLayout {
-  size_t psi, M, Mh, S, tab, part, tw[3], total;
+  size_t psi, M, Mh, S, tab, tw[3], tables_end, part, total;
 };
 
 static BankLayout layout(const int64_t dims[3], int n_unique, int L) {
@@ -108,12 +108,13 @@ static BankLayout layout(const int64_t dims[3], int n_unique, int L) {
   b.tab = o;
   // the synthesis' recursion records, then its order-start masks (packed into doubles)
   o = align256(o + ((size_t)synth_kblocks(L) * 8 * 4 + (synth_kblocks(L) + 1) / 2) * sizeof(double));
-  b.part = o;  // band partials of the synthesis workgroups (3 each), then kappa and S
-  o = align256(o + (3 * ((V + 255) / 256) + 2) * sizeof(double));
   for (int d = 0; d < 3; ++d) {
     b.tw[d] = o;
     o = align256(o + (size_t)dims[d] * 2 * sizeof(float));
   }
+  b.tables_end = o;  // S .. tw: written by the host in one copy
+  b.part = o;        // band partials of the synthesis workgroups (3 each), then kappa and S
+  o = align256(o + (3 * ((V + 255) / 256) + 2) * sizeof(double));
   b.total = o;
   return b;
 }
@@ -231,35 +232,32 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   b->synth_scale = (float)std::ldexp(1.0, -(13 + eS));
   b->kblocks = synth_kblocks(L);
   const int ncb = synth_padded_blocks(b->Npad / 16);
+  // everything the host writes, at its place in the bank buffer after S
+  std::vector<char> stage(lay.tables_end - lay.S, 0);
+  auto at = [&](size_t offset) { return stage.data() + (offset - lay.S); };
   // operand order of v_mfma_f32_16x16x32_f16's B: lane t holds column t % 16
-  // and the eight K entries 8 (t / 16) .. + 7, two per word (low half first)
-  std::vector<uint32_t> S((size_t)b->kblocks * ncb * 2 * 64 * 4, 0u);
+  // and the eight K entries 8 (t / 16) .. + 7, one 16-bit half each
+  _Float16* S = (_Float16*)at(lay.S);
+  const double scale = std::ldexp(1.0, eS);
   const std::vector<int> order = synth_word_order(L);
   for (int kb = 0; kb < b->kblocks; ++kb)
-    for (int cb = 0; cb < ncb; ++cb)
-      for (int t = 0; t < 64; ++t) {
-        const int col = cb * 16 + (t & 15);
-        for (int j = 0; j < 8; ++j) {
-          const int e = kb * 32 + 8 * (t >> 4) + j;  // entry: word e / 2, cos (even) or sin (odd)
-          const int lm = order[e >> 1];
-          const int l = lm / (L + 1), m = lm % (L + 1);
-          const bool sn = (e & 1) == 1;
-          float v = 0.f;
-          if (col < b->n_unique && lm >= 0 && !(m == 0 && sn)) {
-            const int idx = l * l + l + (sn ? -m : m);
-            v = (float)std::ldexp(Sstd[(size_t)idx * b->n_unique + col], eS);
-          }
-          const _Float16 hi = (_Float16)v;
-          const _Float16 lo = (_Float16)(v - (float)hi);
-          uint16_t hb, lb;
-          std::memcpy(&hb, &hi, 2);
-          std::memcpy(&lb, &lo, 2);
-          const size_t w = ((((size_t)kb * ncb + cb) * 2) * 64 + t) * 4 + j / 2;
-          const int sh = (j & 1) * 16;
-          S[w] |= (uint32_t)hb << sh;
-          S[w + 64 * 4] |= (uint32_t)lb << sh;
-        }
+    for (int k = 0; k < 32; ++k) {
+      const int lm = order[(kb * 32 + k) >> 1];  // entry k: word k / 2, cos (even) or sin (odd)
+      const int l = lm / (L + 1), m = lm % (L + 1);
+      const bool sn = (k & 1) == 1;
+      if (lm < 0 || (m == 0 && sn)) continue;
+      const double* row = &Sstd[(size_t)(l * l + l + (sn ? -m : m)) * b->n_unique];
+      for (int col = 0; col < b->n_unique; ++col) {
+        // rounded to float, then to half (the compiler otherwise rounds once, from double)
+        volatile float rounded = (float)(row[col] * scale);
+        const float v = rounded;
+        const _Float16 hi = (_Float16)v;
+        const size_t o =
+            ((((size_t)kb * ncb + col / 16) * 2) * 64 + (size_t)(k / 8) * 16 + col % 16) * 8 + (size_t)(k % 8);
+        S[o] = hi;
+        S[o + 64 * 8] = (_Float16)(v - (float)hi);
       }
+    }
   ShTables t = sh_tables(L);
   // the recursion steps in the synthesis order, per word pair the records
   // (c0, c1) of chains A and B, Q = c0 (z Q') - c1 Q'': inside an order
@@ -269,7 +267,7 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   // (the chain then also multiplies its (x + iy)^m by x + iy, except at its
   // first order)
   const int M = synth_split(L);
-  std::vector<double> tab((size_t)b->kblocks * 8 * 4 + (b->kblocks + 1) / 2, 0.0);
+  double* tab = (double*)at(lay.tab);
   std::vector<uint32_t> starts(b->kblocks, 0u);
   auto put_chain = [&](int chain, int m0, int m1) {
     int i = 0;
@@ -289,24 +287,20 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   };
   put_chain(0, 0, M);
   put_chain(1, M + 1, L);
-  std::memcpy(&tab[(size_t)b->kblocks * 8 * 4], starts.data(), starts.size() * sizeof(uint32_t));
+  std::memcpy(tab + (size_t)b->kblocks * 8 * 4, starts.data(), starts.size() * sizeof(uint32_t));
   b->synth_mb = M + 1;
-  std::vector<float> tw[3];
   for (int d = 0; d < 3; ++d) {
     const int N = (int)dims[d];
-    tw[d].resize(2 * N);
+    float* tw = (float*)at(lay.tw[d]);
     for (int j = 0; j < N; ++j) {
       const double ang = -2.0 * 3.14159265358979323846 * (double)j / (double)N;
-      tw[d][2 * j] = (float)std::cos(ang);
-      tw[d][2 * j + 1] = (float)std::sin(ang);
+      tw[2 * j] = (float)std::cos(ang);
+      tw[2 * j + 1] = (float)std::sin(ang);
     }
   }
   hipStream_t st = (hipStream_t)stream;
-  bool ok = hipMemcpyAsync(b->d.S, S.data(), S.size() * sizeof(uint32_t), hipMemcpyHostToDevice, st) == hipSuccess &&
-            hipMemcpyAsync(b->d.tab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, st) == hipSuccess;
-  for (int d = 0; d < 3 && ok; ++d)
-    ok = hipMemcpyAsync(b->d.tw[d], tw[d].data(), tw[d].size() * sizeof(float), hipMemcpyHostToDevice, st) ==
-         hipSuccess;
+  const bool ok =
+      hipMemcpyAsync(base + lay.S, stage.data(), stage.size(), hipMemcpyHostToDevice, st) == hipSuccess;
   if (!ok) {
     delete b;
     return (os3d_status)fail(OS3D_EDEVICE, "os3d_build_bank: host-to-device copy failed");

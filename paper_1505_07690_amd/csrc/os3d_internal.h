@@ -21,8 +21,6 @@ constexpr int kMaxDim = 4096;
 double bspline(int k, double x);
 void legendre(int L, double x, double* P);               // P[0..L]
 std::vector<double> geodesic_icosahedron(int freq);      // 3 * (10 freq^2 + 2)
-bool zonal_fit(int L, const std::vector<double>& pts, const std::vector<double>& values,
-               std::vector<double>& c);                   // least squares, Householder QR
 void cake_coeffs(int L, const double* c, int variant, double* a);
 void wavelet_coeffs(const os3d_wavelet_params& p, std::vector<double>& c, std::vector<double>& a);
 
