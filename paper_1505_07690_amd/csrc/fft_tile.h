@@ -61,6 +61,7 @@ struct TileArgs {
   long long dn;        // elements between consecutive points of a line
   int chunks;          // y lines: workgroups along x (per z plane); z lines: all workgroups
   int groups;          // workgroups that share the pairs of a launch
+  int two;             // the LDS holds two tiles: successive pairs alternate, one barrier a pair less
   const float2* part;  // partial orientation sums of the groups 1.. (volumes)
   int nparts;          // how many of them the inverse pass adds to its source
   int finish;          // the orientation sum goes on through the division and the inverse DFT

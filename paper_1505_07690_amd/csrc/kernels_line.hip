@@ -38,7 +38,7 @@ __device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
   t.c = threadIdx.x & ((1 << a.lw) - 1);
   t.b = threadIdx.x >> a.lw;
   t.buf = lds;
-  t.tw = lds + (z.N << a.lw);
+  t.tw = lds + ((z.N << a.lw) << a.two);
   t.fq = (u16*)(t.tw + z.N);
   t.red = (float*)(t.fq + ((z.N + 1) & ~1));
   for (int i = threadIdx.x; i < z.N; i += blockDim.x) {
@@ -47,6 +47,20 @@ __device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
   }
   __syncthreads();
   return t;
+}
+
+// Before the tile of the i-th pair is written: the other tile, whose reads
+// ended before the barrier of the pair in between, or this one after a barrier.
+// Two tiles let a wave go on to the next pair while others still transform
+// this one (a stage of N / R butterflies leaves waves idle where the factors
+// differ).
+__device__ __forceinline__ void next_tile(const TileArgs& a, const LineTile& t0, LineTile& t, int i) {
+  if (a.two) {
+    t.buf = t0.buf + (i & 1) * (a.y.N << a.lw);
+    t.red = t0.red + (i & 1) * 16;
+  } else {
+    __syncthreads();
+  }
 }
 
 // The stages between the first and the last factor are chosen at run time;
@@ -197,7 +211,8 @@ __global__ __launch_bounds__(1024) void k_line_mul(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& z = a.y;
-  const LineTile t = line_tile(a, lds);
+  const LineTile t0 = line_tile(a, lds);
+  LineTile t = t0;
   const long long line = ((long long)blockIdx.x << a.lw) + t.c;
   const bool valid = line < a.lines;
   const long long col = valid ? line : a.lines - 1;
@@ -223,7 +238,7 @@ __global__ __launch_bounds__(1024) void k_line_mul(TileArgs a) {
       const float* row = p.psi + (long long)p.rows[j + 1] * p.V + col;
       each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = row[o]; });
     }
-    __syncthreads();  // the previous pair's reads of the tile are done
+    next_tile(a, t0, t, j - j0 + 1);  // (the DFT of f used the first one)
     float2* T = p.dst_c + (long long)j * p.dst_stride + col;
     line_dit<true>(z, t, a.dn, v, [&](long long o, float2 w) {
       if (valid) T[o] = w;
@@ -259,7 +274,8 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& z = a.y;
-  const LineTile t = line_tile(a, lds);
+  const LineTile t0 = line_tile(a, lds);
+  LineTile t = t0;
   const long long line = ((long long)blockIdx.x << a.lw) + t.c;
   const bool valid = line < a.lines;
   const long long col = valid ? line : a.lines - 1;
@@ -273,7 +289,7 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
     const float2* T = p.src_c + (long long)j * p.src_stride + col;
     float ps[RL];
     float2 v[RL];
-    if (j > j0) __syncthreads();  // the previous pair's reads of the tile are done
+    if (j > j0) next_tile(a, t0, t, j - j0);
     line_dif<false>(
         z, t, a.dn, [&](long long o) { return ldnt(T + o); },
         [&]() { each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = ldnt(row + o); }); }, v);
@@ -379,8 +395,9 @@ __global__ __launch_bounds__(1024) void k_line_mul_seq(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& z = a.y;
-  const LineTile t = line_tile(a, lds);
-  u16* pos = (u16*)(t.red + 16);  // position of a frequency
+  const LineTile t0 = line_tile(a, lds);
+  LineTile t = t0;
+  u16* pos = (u16*)(t.red + 32);  // position of a frequency
   for (int i = threadIdx.x; i < z.N; i += blockDim.x) pos[t.fq[i]] = (u16)i;
   const long long line = ((long long)blockIdx.x << a.lw) + t.c;
   const bool valid = line < a.lines;
@@ -392,17 +409,17 @@ __global__ __launch_bounds__(1024) void k_line_mul_seq(TileArgs a) {
 #pragma unroll
   for (int r = 0; r < R0; ++r) spec[r] = p.src_c[o0 + r * step0 + col];
   seq_butterfly<R0, RB0>(spec, t.tw, 0, z.S[0], 1, true, -p.sgn);
-  float2* q0 = t.buf + (b0 << t.lw) + t.c;
-  const int d0 = z.S[0] << t.lw;
+  const int d0 = z.S[0] << t.lw, q0 = (b0 << t.lw) + t.c;
   if (first) {
 #pragma unroll
-    for (int r = 0; r < R0; ++r) q0[r * d0] = spec[r];
+    for (int r = 0; r < R0; ++r) t.buf[q0 + r * d0] = spec[r];
   }
   line_seq_rest<true>(z, t, a.dn, -p.sgn, [](long long, float2) {});
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R0; ++r) spec[r] = t.buf[(pos[b0 + r * z.S[0]] << t.lw) + t.c];
   conj_twiddles(z, t);
+  if (a.two) __syncthreads();
   const int j0 = (int)((long long)p.nb * blockIdx.y / a.groups);
   const int j1 = (int)((long long)p.nb * (blockIdx.y + 1) / a.groups);
   float ps[R0];
@@ -430,14 +447,14 @@ __global__ __launch_bounds__(1024) void k_line_mul_seq(TileArgs a) {
     for (int r = 0; r < R0; ++r) s += __builtin_amdgcn_sqrtf(v[r].x * v[r].x + v[r].y * v[r].y);
     if (!valid || !first) s = 0.f;
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    __syncthreads();  // the previous pair's reads of the tile (and of red) are done
+    next_tile(a, t0, t, j - j0 + 1);  // and red
     if ((threadIdx.x & 63) == 0) t.red[threadIdx.x >> 6] = s;
     seq_butterfly<R0, RB0>(v, t.tw, 0, z.S[0], 1, true, p.sgn);
     float2* T = p.dst_c + (long long)j * p.dst_stride + col;
     if (z.nst > 1) {
       if (first) {
 #pragma unroll
-        for (int r = 0; r < R0; ++r) q0[r * d0] = v[r];
+        for (int r = 0; r < R0; ++r) t.buf[q0 + r * d0] = v[r];
       }
     } else if (first && valid) {
 #pragma unroll
@@ -511,7 +528,7 @@ static int check_line(const char* what) {
 }
 
 struct LinePlan {
-  int lw, threads;
+  int lw, threads, two;
   size_t lds;
   // workgroups that keep the chip busy: eight waves per CU (64^3 x 21 pairs: 95
   // us a job, 97 with thirty-two; 96 x 80 x 64 x 81: 708 and 724)
@@ -541,7 +558,10 @@ static LinePlan line_plan(const AxisT& z, long long lines) {
   LinePlan q;
   q.lw = lw;
   q.threads = std::min(1024, ((nbf << lw) + 63) / 64 * 64);
-  q.lds = ((size_t)z.N << lw) * 8 + (size_t)z.N * 8 + (size_t)((z.N + 1) & ~1) * 4 + 64;
+  const size_t tile = ((size_t)z.N << lw) * 8, tables = (size_t)z.N * 8 + (size_t)((z.N + 1) & ~1) * 4 + 128;
+  // a second tile where two workgroups still share a CU
+  q.two = (z.nst > 1 && 2 * (2 * tile + tables) <= 160 * 1024) ? 1 : 0;
+  q.lds = (tile << q.two) + tables;
   return q;
 }
 
@@ -553,6 +573,7 @@ static TileArgs zline_args(const os3d_bank* b, const PassArgs& p, LinePlan& q, b
   a.dn = a.lines;
   q = line_plan(a.y, a.lines);
   a.lw = q.lw;
+  a.two = q.two;
   a.chunks = (int)((a.lines + (1LL << q.lw) - 1) >> q.lw);
   a.groups = 1;
   return a;
@@ -616,7 +637,8 @@ int launch_yline(const os3d_bank* b, const PassArgs& p, bool seq, hipStream_t st
   a.y = seq ? make_axis_seq((int)b->dims[1], b->d.tw[1]) : make_axis((int)b->dims[1], b->d.tw[1]);
   a.dn = b->dims[2];
   a.lines = b->dims[0] * b->dims[2];
-  const LinePlan q = line_plan(a.y, a.lines);
+  LinePlan q = line_plan(a.y, a.lines);
+  if (q.two) q.lds -= ((size_t)a.y.N << q.lw) * 8;  // one pair per workgroup
   a.lw = q.lw;
   a.chunks = (int)((b->dims[2] + (1LL << q.lw) - 1) >> q.lw);
   const long long tiles = a.chunks * b->dims[0];
