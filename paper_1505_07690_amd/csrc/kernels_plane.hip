@@ -228,6 +228,11 @@ __device__ __forceinline__ void plane_put(float2* P, int t, const float2 (&v)[16
   }
 }
 
+// Task of a workgroup's step.
+__device__ __forceinline__ int plane_task(const PassArgs& a, int ntask, int step) {
+  return a.newest_first ? ntask - 1 - step : step;
+}
+
 // Persistent over tasks (pair slot j, z plane): task = j * Nz + z, strided
 // by the grid; the loads of task + gridDim.x are issued before the current
 // plane's LDS stages and stores.  INV: inverse DFT (+1 exponent).
@@ -243,12 +248,14 @@ __global__ __launch_bounds__(PlaneCfg<NP>::T) void k_plane(PassArgs a) {
   // to the transform's registers: that pass loads its plane when it starts it
   constexpr bool kPrefetch = !(LM == LM_UIN && DT == OS3D_C64 && NP == 128);
   PlaneIn<LM, DT> in;
-  int task = blockIdx.x;
-  if (kPrefetch && task < ntask) {
-    in.issue(a, task / a.Nz, (long long)(task % a.Nz) * NP * NP + t, C::T);
-    in.issue2(a, task / a.Nz, (long long)(task % a.Nz) * NP * NP + t, C::T);
+  int step = blockIdx.x;
+  const int first = plane_task(a, ntask, step);
+  if (kPrefetch && step < ntask) {
+    in.issue(a, first / a.Nz, (long long)(first % a.Nz) * NP * NP + t, C::T);
+    in.issue2(a, first / a.Nz, (long long)(first % a.Nz) * NP * NP + t, C::T);
   }
-  for (; task < ntask; task += gridDim.x) {
+  for (; step < ntask; step += gridDim.x) {
+    const int task = plane_task(a, ntask, step);
     const int j = task / a.Nz;
     const long long base = (long long)(task % a.Nz) * NP * NP;
     if (!kPrefetch) {
@@ -260,15 +267,16 @@ __global__ __launch_bounds__(PlaneCfg<NP>::T) void k_plane(PassArgs a) {
       in.get(a, j, v);
       plane_put<NP>(P, t, v);
     }
-    const int next = task + gridDim.x;
-    if (kPrefetch && next < ntask) in.issue(a, next / a.Nz, (long long)(next % a.Nz) * NP * NP + t, C::T);
+    const bool more = step + gridDim.x < ntask;
+    const int next = plane_task(a, ntask, step + gridDim.x);
+    if (kPrefetch && more) in.issue(a, next / a.Nz, (long long)(next % a.Nz) * NP * NP + t, C::T);
     __syncthreads();
     plane_rows<NP, INV>(P, twl, t);
     __syncthreads();
     plane_cols<NP, INV>(
         P, twl, t,
         [&]() {
-          if (kPrefetch && next < ntask) in.issue2(a, next / a.Nz, (long long)(next % a.Nz) * NP * NP + t, C::T);
+          if (kPrefetch && more) in.issue2(a, next / a.Nz, (long long)(next % a.Nz) * NP * NP + t, C::T);
         },
         [&](int jj, int x, const float2 (&u)[C::R2]) {
           float2 dummy[C::R2];

@@ -286,7 +286,8 @@ __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
   const TileLds t = tile_lds<PLANE>(a, lds, SEQ && INV);
   const int n = a.rows * a.x.N, lx = a.x.nst - 1, ly = a.y.nst - 1;
   const long long ntask = a.tiles * p.nb;
-  for (long long task = blockIdx.x; task < ntask; task += gridDim.x) {
+  for (long long step = blockIdx.x; step < ntask; step += gridDim.x) {
+    const long long task = p.newest_first ? ntask - 1 - step : step;
     const int j = (int)(task / a.tiles);
     const long long tile = task - j * a.tiles, g0 = tile * n;
     if constexpr (!PLANE) {
