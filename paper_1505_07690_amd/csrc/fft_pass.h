@@ -21,6 +21,7 @@ struct PassArgs {
   const float2* tw;     // exp(-2 pi i j / N) of the x axis
   float sgn;            // -1: forward DFT, +1: inverse DFT
   int nb;               // pairs in this launch
+  int split;            // factor B of the y axis that the z-line passes take (0: none)
   int newest_first;     // the pairs in descending order (their source was written in ascending order)
   // sources
   const float* src_r;

@@ -49,7 +49,8 @@ struct AxisT {
   unsigned mS[kMaxStages];      // fast division by S
   int nf, F[kMaxFactors];       // single factors
   unsigned mF[kMaxFactors];
-  const float2* tw;             // exp(-2 pi i j / N)
+  const float2* tw;             // exp(-2 pi i j / N) at tw[j tws]
+  int tws;
 };
 
 struct TileArgs {
@@ -57,9 +58,11 @@ struct TileArgs {
   AxisT x, y;     // x: the contiguous axis of a tile; y: its row axis (the line axis of a line kernel)
   // line kernels (y or z lines): W = 2^lw lines side by side per workgroup
   int lw;
-  long long lines;     // lines per volume
+  int lb;              // split passes: 2^lb of the 2^lw lines are one residue class of y
+  long long lines;     // lines per volume (split: per class member)
   long long dn;        // elements between consecutive points of a line
   int chunks;          // y lines: workgroups along x (per z plane); z lines: all workgroups
+  int xcd;             // chunks of an XCD (0: in the order of the workgroups)
   int groups;          // workgroups that share the pairs of a launch
   int two;             // the LDS holds two tiles: successive pairs alternate, one barrier a pair less
   const float2* part;  // partial orientation sums of the groups 1.. (volumes)
@@ -68,6 +71,8 @@ struct TileArgs {
   // plane and row kernels
   int rows, P, A;      // rows = P A rows of x.N values per tile
   int RS, pad;         // LDS row stride; values skipped after every x.R[last]
+  int B;                 // split passes: tile of class yb = rows yb, yb + B, ... of its plane in space
+  unsigned mB;
   unsigned mrows, mNx, mRL, mP, mA, mnf;
   long long tiles;     // tiles per volume
   long long nlines;    // x lines per volume
@@ -328,6 +333,7 @@ inline void set_stages(AxisT& a, int N, const float* tw) {
   }
   for (int i = 0; i < a.nf; ++i) a.mF[i] = fdiv_mul((unsigned)a.F[i]);
   a.tw = (const float2*)tw;
+  a.tws = 1;
 }
 
 // The balanced schedule.  odd_last moves an odd factor to the end: the

@@ -192,7 +192,7 @@ static int timed(hipStream_t st, int kid, double alg, F f) {
 template <int LM, int SM>
 static int run_xy(const os3d_bank* b, int kid, double alg, const PassArgs& a, bool seq, hipStream_t st) {
   return timed(st, kid, alg, [&]() -> int {
-    if (b->plane != kPlaneFixed) return launch_tile<LM, SM>(b, a, b->plane == kPlaneTile, seq, st);
+    if (b->plane != kPlaneFixed) return launch_tile<LM, SM>(b, a, b->plane == kPlaneTile || a.split, seq, st);
     launch_plane<LM, SM>(a, a.nb, st);
     return OS3D_OK;
   });
@@ -272,6 +272,7 @@ static int sum_pairs(const os3d_bank* b, const PassArgs& pairs, const float2* T,
                  [&]() -> int { return launch_zline_acc(b, z, parts, groups, finish, st); });
   if (rc || !last || finish) return rc;
   z.src_c = X;
+  z.split = 0;
   return timed(st, kProfInvFirst, 0.0, [&]() -> int { return launch_zline_div(b, z, parts, groups - 1, st); });
 }
 
@@ -293,6 +294,7 @@ int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int d
     for (int r0 = 0; r0 < b->n_unique; r0 += nbmax) {
       PassArgs z = pass_args(b, 1.f, std::min(nbmax, b->n_unique - r0));
       set_pairs(b, z, r0);
+      z.split = quant ? 0 : b->split;
       z.src_c = F;
       z.dst_c = T;
       z.dst_stride = V;
@@ -307,13 +309,13 @@ int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int d
       }
       z.src_c = T;
       z.src_stride = V;
-      if (!b->plane && (rc = run_y(b, kProfFwdMid, z, quant, st))) return rc;
+      if (!b->plane && !z.split && (rc = run_y(b, kProfFwdMid, z, quant, st))) return rc;
       // the pass before wrote T in ascending order: its last pairs are still in
       // the last-level cache (256 MB), so this one begins with them.  96 x 80 x 64
       // x 162, forward + reconstruction: 654 -> 611 us; 160 x 128 x 128 x 42: 672
-      // -> 656.  With a pass over y between them (larger planes) reversing any of
-      // the passes gave nothing or lost 2 %.
-      z.newest_first = b->plane ? 1 : 0;
+      // -> 656.  With a pass over y between them reversing any of the passes gave
+      // nothing or lost 2 %.
+      z.newest_first = b->plane || z.split ? 1 : 0;
       z.Uout = (char*)U + (size_t)bi * b->n_orients * V * ubytes;
       z.dtype = dtype;
       z.scales = quant ? sc : nullptr;
@@ -351,6 +353,7 @@ int launch_reduce(const os3d_bank* b, const void* U, int dtype, const float* sca
     for (int r0 = 0; r0 < b->n_unique; r0 += nbmax) {
       PassArgs x = pass_args(b, -1.f, std::min(nbmax, b->n_unique - r0));
       set_pairs(b, x, r0);
+      x.split = b->split;
       x.U = (const char*)U + (size_t)bi * b->n_orients * V * ubytes;
       x.dtype = dtype;
       x.scales = (dtype == OS3D_C64) ? nullptr : scales + (long long)bi * b->n_orients;
@@ -359,7 +362,7 @@ int launch_reduce(const os3d_bank* b, const void* U, int dtype, const float* sca
       if ((rc = run_xy<LM_UIN, SM_C>(b, kProfRecFirst, score_bytes(x, ubytes), x, false, st))) return rc;
       x.src_c = T;
       x.src_stride = V;
-      if (!b->plane && (rc = run_y(b, kProfRecMid, x, false, st))) return rc;
+      if (!b->plane && !x.split && (rc = run_y(b, kProfRecMid, x, false, st))) return rc;
       if ((rc = sum_pairs(b, x, T, X, parts, groups, r0 == 0, r0 + nbmax >= b->n_unique, divide_M, st))) return rc;
     }
     if ((rc = planes_to_f(b, X, f_out + (long long)bi * V, st))) return rc;
@@ -389,24 +392,25 @@ int launch_process(const os3d_bank* b, const float* f, int batch, int phi_kind, 
     for (int r0 = 0; r0 < b->n_unique; r0 += nbp) {
       PassArgs z = pass_args(b, 1.f, std::min(nbp, b->n_unique - r0));
       set_pairs(b, z, r0);
+      z.split = b->split;
       z.src_c = F;
       z.dst_c = T;
       z.dst_stride = V;
       if ((rc = timed(st, kProfFwdFirst, 0.0, [&]() -> int { return launch_zline_mul(b, z, st); }))) return rc;
       z.src_c = T;
       z.src_stride = V;
-      if (!b->plane && (rc = run_y(b, kProfFwdMid, z, false, st))) return rc;
+      if (!b->plane && !z.split && (rc = run_y(b, kProfFwdMid, z, false, st))) return rc;
       z.out_scale = 1.f / (float)V;
       z.phi_kind = phi_kind;
       z.phi_p = phi_p;
       rc = timed(st, kProfFwdLast, 0.0, [&]() -> int {
-        if (b->plane != kPlaneFixed) return launch_tile_phi(b, z, b->plane == kPlaneTile, st);
+        if (b->plane != kPlaneFixed) return launch_tile_phi(b, z, b->plane == kPlaneTile || z.split, st);
         launch_plane_phi(z, z.nb, st);
         return OS3D_OK;
       });
       if (rc) return rc;
       z.sgn = -1.f;
-      if (!b->plane && (rc = run_y(b, kProfRecMid, z, false, st))) return rc;
+      if (!b->plane && !z.split && (rc = run_y(b, kProfRecMid, z, false, st))) return rc;
       if ((rc = sum_pairs(b, z, T, X, parts, groups, r0 == 0, r0 + nbp >= b->n_unique, true, st))) return rc;
     }
     if ((rc = planes_to_f(b, X, f_out + (long long)bi * V, st))) return rc;

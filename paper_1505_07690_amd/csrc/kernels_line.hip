@@ -9,6 +9,15 @@
 // are bound by memory (a value costs one 8-byte read or write, its bank row
 // entry and about 70 flops): the spectrum of a tile (k_line_mul) or its
 // orientation sum (k_line_acc) stays in registers over the pairs of a launch.
+//
+// Split passes.  A (y, x) plane larger than LDS would take a pass over y and
+// one over x.  Instead Ny = B A: the z-line passes take the factor B as well
+// (a tile is W lines of each of the B rows ka + kb A) and the plane pass
+// transforms the A rows of one class along y and x in LDS (kernels_tile.hip), so
+// the intermediate goes through memory once, not twice, for one more stage
+// in LDS.  Forward + reconstruction of 180 x 240 x 216 x 42 (B = 4): 4.73 -> 3.65
+// ms, 64 x 320 x 320 (B = 8): 3.27 -> 2.59 ms.  The forward into 16-bit scores
+// keeps three passes: its order of sums is fixed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,10 +35,22 @@ typedef unsigned short u16;
 struct LineTile {
   float2* buf;
   float2* tw;
+  float2* ts;  // split: twiddle between the classes and the z lines, per line
   u16* fq;
   float* red;
   int b, c, lw;  // butterfly, line of this thread
 };
+
+// The chunk of lines of a workgroup.  Workgroups go to the eight XCDs in turn,
+// and each XCD has an L2 of its own: a run of a.xcd neighbouring chunks is given
+// to each, so that the cache lines that two chunks share (runs start anywhere in
+// a line of 128 bytes when Nx is no multiple of 16, and 16 bank entries are half a
+// line) are fetched by one XCD and their stores merge there.  Forward +
+// reconstruction of 256 x 192 x 192 x 42: 3.73 -> 3.56 ms, 64 x 320 x 320: 2.59 ->
+// 2.48 ms; processing of 120 x 100 x 90: 306 -> 295 us; 128^3: unchanged.
+__device__ __forceinline__ int chunk_of(const TileArgs& a) {
+  return a.xcd ? (int)(blockIdx.x & 7) * a.xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+}
 
 __device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
   const AxisT& z = a.y;
@@ -39,14 +60,32 @@ __device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
   t.b = threadIdx.x >> a.lw;
   t.buf = lds;
   t.tw = lds + ((z.N << a.lw) << a.two);
-  t.fq = (u16*)(t.tw + z.N);
+  t.ts = t.tw + z.N;
+  t.fq = (u16*)(t.ts + (a.lb ? 1 << a.lw : 0));
   t.red = (float*)(t.fq + ((z.N + 1) & ~1));
   for (int i = threadIdx.x; i < z.N; i += blockDim.x) {
     t.tw[i] = z.tw[i];
     t.fq[i] = (u16)freq_of(z, i);
   }
+  if (a.lb) {
+    const int w = a.lw - a.lb;
+    for (int i = threadIdx.x; i < 1 << a.lw; i += blockDim.x) {
+      const long long line = min(((long long)chunk_of(a) << w) + (i & ((1 << w) - 1)), a.lines - 1);
+      t.ts[i] = a.x.tw[(int)line / a.p.Nx * (i >> w)];
+    }
+  }
   __syncthreads();
   return t;
+}
+
+// The thread's line and its offset in a z plane.  Split: line ka Nx + x of
+// every class yb, at the row yb Ny / B + ka of the intermediate (and the row
+// ka + kb Ny / B of the spectrum).
+__device__ __forceinline__ bool line_of(const TileArgs& a, const LineTile& t, long long& col) {
+  const int w = a.lw - a.lb;
+  const long long line = ((long long)chunk_of(a) << w) + (t.c & ((1 << w) - 1));
+  col = min(line, a.lines - 1) + (t.c >> w) * a.lines;
+  return line < a.lines;
 }
 
 // Before the tile of the i-th pair is written: the other tile, whose reads
@@ -92,14 +131,15 @@ __device__ __forceinline__ bool has_last(const AxisT& z, const LineTile& t) {
 // out[r] receives frequency fq[b RL] + r N / RL of its last butterfly b.
 // Offsets are a thread's base plus a scalar per value.  mid() runs after the
 // first stage (its loads then don't hold registers next to that stage's).
-template <bool INV, int RL, class Src, class Mid>
+// IN_LDS: the tile holds the values already.
+template <bool INV, int RL, bool IN_LDS = false, class Src, class Mid>
 __device__ __forceinline__ void line_dif(const AxisT& z, const LineTile& t, long long dn, Src src, Mid mid,
                                          float2 (&out)[RL]) {
   constexpr float sg = INV ? 1.f : -1.f;
   const int last = z.nst - 1, b = butterfly(t);
   if (last == 0) {
 #pragma unroll
-    for (int r = 0; r < RL; ++r) out[r] = src(r * dn);
+    for (int r = 0; r < RL; ++r) out[r] = IN_LDS ? t.buf[(r << t.lw) + t.c] : src(r * dn);
     dft_r<RL>(out, sg);
     mid();
     return;
@@ -109,11 +149,11 @@ __device__ __forceinline__ void line_dif(const AxisT& z, const LineTile& t, long
       constexpr int R = decltype(rc)::value;
       float2 v[R];
       const long long o = b * dn, step = z.S[0] * dn;
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = src(o + r * step);
-      dft_r<R>(v, sg);
       float2* q = t.buf + (b << t.lw) + t.c;
       const int d = z.S[0] << t.lw;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = IN_LDS ? q[r * d] : src(o + r * step);
+      dft_r<R>(v, sg);
 #pragma unroll
       for (int r = 0; r < R; ++r) q[r * d] = v[r];
     });
@@ -151,15 +191,16 @@ __device__ __forceinline__ void line_dif(const AxisT& z, const LineTile& t, long
 
 // DIT of the tile from the registers of the last factor's butterflies;
 // sink(o, v) takes the value at offset o = n dn of the thread's line.  The
-// caller synchronises before the tile's LDS is written again.
-template <bool INV, int RL, class Sink>
+// caller synchronises before the tile's LDS is written again.  TO_LDS: the
+// values stay in the tile, in natural order.
+template <bool INV, int RL, bool TO_LDS = false, class Sink>
 __device__ __forceinline__ void line_dit(const AxisT& z, const LineTile& t, long long dn, float2 (&in)[RL],
                                          Sink sink) {
   constexpr float sg = INV ? 1.f : -1.f;
   const int last = z.nst - 1, b = butterfly(t);
   dft_r<RL>(in, sg);
   if (b * RL < z.N) {
-    if (last == 0) {
+    if (!TO_LDS && last == 0) {
 #pragma unroll
       for (int r = 0; r < RL; ++r) sink(r * dn, in[r]);
     } else {
@@ -182,7 +223,7 @@ __device__ __forceinline__ void line_dit(const AxisT& z, const LineTile& t, long
         for (int r = 0; r < R; ++r) v[r] = q[r * d];
         twiddle<R, INV>(v, t.tw, l * z.tstep[i]);
         dft_r<R>(v, sg);
-        if (i == 0) {
+        if (!TO_LDS && i == 0) {
           const long long o = l * dn, step = S * dn;
 #pragma unroll
           for (int r = 0; r < R; ++r) sink(o + r * step, v[r]);
@@ -203,19 +244,71 @@ __device__ __forceinline__ void each_freq(const AxisT& z, const LineTile& t, lon
   for (int r = 0; r < RL; ++r) get(r, o + r * step);
 }
 
+// f(integral_constant<B>) for the factor 2^lb of y
+template <class F>
+__device__ __forceinline__ void with_split(int lb, F f) {
+  switch (lb) {
+    case 1: f(std::integral_constant<int, 2>{}); break;
+    case 2: f(std::integral_constant<int, 4>{}); break;
+    default: f(std::integral_constant<int, 8>{}); break;
+  }
+}
+
+// The factor B of the y axis on the tile of a split pass: y = yb + B ya, ky =
+// ka + kb Ny / B.  split_out: the inverse DFT over kb -> yb and the twiddle, to
+// memory; split_in: from memory, the twiddle and the DFT over yb -> kb.
+__device__ __forceinline__ void split_out(const TileArgs& a, const LineTile& t, float2* T) {
+  const int w = a.lw - a.lb, c = threadIdx.x & ((1 << w) - 1), nb = blockDim.x >> w;
+  const long long line = ((long long)chunk_of(a) << w) + c;
+  with_split(a.lb, OS3D_RADIX_FN(bc) {
+    constexpr int B = decltype(bc)::value;
+    for (int e = threadIdx.x >> w; e < a.y.N; e += nb) {
+      const float2* q = t.buf + (e << t.lw) + c;
+      float2 v[B];
+#pragma unroll
+      for (int r = 0; r < B; ++r) v[r] = q[r << w];
+      dft_r<B>(v, 1.f);
+#pragma unroll
+      for (int r = 1; r < B; ++r) v[r] = cmulc(v[r], t.ts[(r << w) + c]);
+      if (line < a.lines) {
+#pragma unroll
+        for (int r = 0; r < B; ++r) T[e * a.dn + r * a.lines + line] = v[r];
+      }
+    }
+  });
+}
+__device__ __forceinline__ void split_in(const TileArgs& a, const LineTile& t, const float2* T) {
+  const int w = a.lw - a.lb, c = threadIdx.x & ((1 << w) - 1), nb = blockDim.x >> w;
+  const long long line = min(((long long)chunk_of(a) << w) + c, a.lines - 1);
+  with_split(a.lb, OS3D_RADIX_FN(bc) {
+    constexpr int B = decltype(bc)::value;
+    for (int e = threadIdx.x >> w; e < a.y.N; e += nb) {
+      float2 v[B];
+#pragma unroll
+      for (int r = 0; r < B; ++r) v[r] = ldnt(T + e * a.dn + r * a.lines + line);
+#pragma unroll
+      for (int r = 1; r < B; ++r) v[r] = cmul(v[r], t.ts[(r << w) + c]);
+      dft_r<B>(v, -1.f);
+      float2* q = t.buf + (e << t.lw) + c;
+#pragma unroll
+      for (int r = 0; r < B; ++r) q[r << w] = v[r];
+    }
+  });
+}
+
 // The DFT of f along z (f transformed along y and x), then for every pair:
 // times the bank row, inverse DFT along z -> intermediate (complex64
 // scores and processing; 16-bit scores: k_line_mul_seq).
-template <int RL>
+template <int RL, bool SPLIT>
 __global__ __launch_bounds__(1024) void k_line_mul(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& z = a.y;
+  if (chunk_of(a) >= a.chunks) return;
   const LineTile t0 = line_tile(a, lds);
   LineTile t = t0;
-  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
-  const bool valid = line < a.lines;
-  const long long col = valid ? line : a.lines - 1;
+  long long col;
+  const bool valid = line_of(a, t, col);
   float2 spec[RL];
 #pragma unroll
   for (int r = 0; r < RL; ++r) spec[r] = make_float2(0.f, 0.f);
@@ -239,10 +332,16 @@ __global__ __launch_bounds__(1024) void k_line_mul(TileArgs a) {
       each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = row[o]; });
     }
     next_tile(a, t0, t, j - j0 + 1);  // (the DFT of f used the first one)
-    float2* T = p.dst_c + (long long)j * p.dst_stride + col;
-    line_dit<true>(z, t, a.dn, v, [&](long long o, float2 w) {
-      if (valid) T[o] = w;
-    });
+    if constexpr (SPLIT) {
+      line_dit<true, RL, true>(z, t, a.dn, v, [](long long, float2) {});
+      __syncthreads();
+      split_out(a, t, p.dst_c + (long long)j * p.dst_stride);
+    } else {
+      float2* T = p.dst_c + (long long)j * p.dst_stride + col;
+      line_dit<true>(z, t, a.dn, v, [&](long long o, float2 w) {
+        if (valid) T[o] = w;
+      });
+    }
   }
 }
 
@@ -269,16 +368,16 @@ __device__ __forceinline__ void divide_inverse(const TileArgs& a, const LineTile
 // the workgroup's share of the pairs.  With few lines the pairs of a launch
 // are shared out to `groups` workgroups per tile (a volume of partial sums
 // each, added by k_line_div): 64^3 x 21 pairs has 128 tiles for 256 CUs.
-template <int RL>
+template <int RL, bool SPLIT>
 __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& z = a.y;
+  if (chunk_of(a) >= a.chunks) return;
   const LineTile t0 = line_tile(a, lds);
   LineTile t = t0;
-  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
-  const bool valid = line < a.lines;
-  const long long col = valid ? line : a.lines - 1;
+  long long col;
+  const bool valid = line_of(a, t, col);
   float2 acc[RL];
 #pragma unroll
   for (int r = 0; r < RL; ++r) acc[r] = make_float2(0.f, 0.f);
@@ -290,7 +389,11 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
     float ps[RL];
     float2 v[RL];
     if (j > j0) next_tile(a, t0, t, j - j0);
-    line_dif<false>(
+    if constexpr (SPLIT) {
+      split_in(a, t, p.src_c + (long long)j * p.src_stride);
+      __syncthreads();
+    }
+    line_dif<false, RL, SPLIT>(
         z, t, a.dn, [&](long long o) { return ldnt(T + o); },
         [&]() { each_freq<RL>(z, t, a.dn, [&](int r, long long o) { ps[r] = ldnt(row + o); }); }, v);
     each_freq<RL>(z, t, a.dn, [&](int r, long long) {
@@ -312,9 +415,8 @@ __global__ __launch_bounds__(1024) void k_line_div(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const LineTile t = line_tile(a, lds);
-  const long long line = ((long long)blockIdx.x << a.lw) + t.c;
-  const bool valid = line < a.lines;
-  const long long col = valid ? line : a.lines - 1;
+  long long col;
+  const bool valid = line_of(a, t, col);
   float2 x[RL];
 #pragma unroll
   for (int r = 0; r < RL; ++r) x[r] = make_float2(0.f, 0.f);
@@ -565,16 +667,55 @@ static LinePlan line_plan(const AxisT& z, long long lines) {
   return q;
 }
 
+// Split passes (p.split = B): tiles of B classes x W lines, W = 32, or 16 where
+// the LDS or 1024 threads don't hold that (100 x 180 x 180, B = 2: 1.31 ms a job
+// with 32, 1.47 with 16).  Runs of 8 lose what the pass over y costs: 256 x 192 x
+// 192 takes 4.4 ms with them, 4.2 in three passes and 3.7 with runs of 16.
+static bool split_plan(const AxisT& z, int B, LinePlan& q, int& lb) {
+  int rmin = 16;
+  for (int i = 0; i < z.nst; ++i) rmin = std::min(rmin, z.R[i]);
+  const int nbf = z.N / rmin;
+  for (lb = 0; (1 << lb) < B;) ++lb;
+  for (int w = 5; w >= 4; --w) {
+    q.lw = lb + w;
+    q.threads = ((nbf << q.lw) + 63) / 64 * 64;
+    const size_t tile = ((size_t)z.N << q.lw) * 8;
+    const size_t tables = (size_t)z.N * 8 + ((size_t)8 << q.lw) + (size_t)((z.N + 1) & ~1) * 4 + 128;
+    q.two = (z.nst > 1 && 2 * (2 * tile + tables) <= 160 * 1024) ? 1 : 0;
+    q.lds = (tile << q.two) + tables;
+    if (q.threads <= 1024 && q.lds <= 160 * 1024) return true;
+  }
+  return false;
+}
+
+// The smallest B = 2, 4, 8 that leaves planes of Ny / B rows in LDS (a larger
+// one only widens the z-line tiles: 100 x 180 x 180 takes 1.43 ms a job with B = 4,
+// 1.82 with 8).  None: the pairs take three passes (z lines, y lines, x lines).
+int split_factor(int Nz, int Ny, int Nx) {
+  for (int B = 2; B <= 8; B *= 2) {
+    LinePlan q;
+    int lb;
+    if (Ny % B == 0 && plane_fits(Ny / B, Nx) && split_plan(make_axis(Nz, nullptr), B, q, lb)) return B;
+  }
+  return 0;
+}
+
 static TileArgs zline_args(const os3d_bank* b, const PassArgs& p, LinePlan& q, bool seq = false) {
   TileArgs a = {};
   a.p = p;
   a.y = seq ? make_axis_seq((int)b->dims[0], b->d.tw[0]) : make_axis((int)b->dims[0], b->d.tw[0]);
   a.lines = b->dims[1] * b->dims[2];
   a.dn = a.lines;
-  q = line_plan(a.y, a.lines);
+  if (p.split) {
+    split_plan(a.y, p.split, q, a.lb);
+    a.lines /= p.split;
+    a.x.tw = (const float2*)b->d.tw[1];
+  } else {
+    q = line_plan(a.y, a.lines);
+  }
   a.lw = q.lw;
   a.two = q.two;
-  a.chunks = (int)((a.lines + (1LL << q.lw) - 1) >> q.lw);
+  a.chunks = (int)((a.lines + (1LL << (q.lw - a.lb)) - 1) >> (q.lw - a.lb));
   a.groups = 1;
   return a;
 }
@@ -589,9 +730,13 @@ int zline_tiles(const os3d_bank* b, bool seq) {
 // its read).
 int zline_acc_groups(const os3d_bank* b, int nb) {
   LinePlan q;
-  const TileArgs a = zline_args(b, PassArgs{}, q);
+  PassArgs p = {};
+  p.split = b->split;
+  const TileArgs a = zline_args(b, p, q);
   return (int)std::max(1LL, std::min<long long>(std::min(8, nb / 3), q.fill() / a.chunks));
 }
+
+static int xcd_share(const TileArgs& a) { return (a.chunks + 7) / 8; }
 
 int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
   LinePlan q;
@@ -600,13 +745,17 @@ int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
   // the forward DFT is repeated by every workgroup of a tile: share the
   // pairs only as far as it takes to fill the chip
   a.groups = (int)std::max(1LL, std::min<long long>(p.nb, (q.fill() + a.chunks - 1) / a.chunks));
-  const dim3 grid((unsigned)a.chunks, (unsigned)a.groups);
+  if (!seq) a.xcd = xcd_share(a);
+  const dim3 grid((unsigned)(seq ? a.chunks : 8 * a.xcd), (unsigned)a.groups);
   if (seq)
     with_seq(a.y.R[0], a.y.RB[0], [&](auto rc, auto rb) {
       launch_line(k_line_mul_seq<decltype(rc)::value, decltype(rb)::value>, grid, q, a, st);
     });
   else
-    with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_mul<decltype(rc)::value>, grid, q, a, st); });
+    with_radix(a.y.R[a.y.nst - 1], [&](auto rc) {
+      constexpr int RL = decltype(rc)::value;
+      launch_line(p.split ? k_line_mul<RL, true> : k_line_mul<RL, false>, grid, q, a, st);
+    });
   return check_line("k_line_mul");
 }
 
@@ -616,8 +765,12 @@ int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* parts, int g
   a.groups = groups;
   a.part = parts;
   a.finish = finish ? 1 : 0;
-  const dim3 grid((unsigned)a.chunks, (unsigned)a.groups);
-  with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_acc<decltype(rc)::value>, grid, q, a, st); });
+  a.xcd = xcd_share(a);
+  const dim3 grid((unsigned)(8 * a.xcd), (unsigned)a.groups);
+  with_radix(a.y.R[a.y.nst - 1], [&](auto rc) {
+    constexpr int RL = decltype(rc)::value;
+    launch_line(p.split ? k_line_acc<RL, true> : k_line_acc<RL, false>, grid, q, a, st);
+  });
   return check_line("k_line_acc");
 }
 

@@ -2,7 +2,8 @@
 // fft_tile.h).  A tile is a run of rows of Nx consecutive values: one or
 // more whole (y, x) planes, transformed along both axes while they sit in
 // LDS (one round trip of the intermediate instead of two), or, for planes
-// larger than LDS, rows transformed along x alone.  y goes before x: the loads
+// larger than LDS, one class of their rows (yb, yb + B, ..: kernels_line.hip,
+// "split passes") or rows transformed along x alone.  y goes before x: the loads
 // are whole rows then, and the shorter runs are the stores' (the pair load of
 // 96 x 80 x 64 x 41 pairs: 108 us, 117 with x first); only the spectrum of a
 // volume whose scores are stored in 16 bits takes x first (its order is fixed).
@@ -51,6 +52,24 @@ struct TileLds {
   u16* ys;  // frequency ky -> row after the DIF
 };
 
+// Where the rows of a tile lie in space: row r of the tile at g + r d.  Split
+// planes: the tile of class yb holds the rows yb + B r (elsewhere, in the
+// intermediate, its rows are consecutive).
+struct RowMap {
+  long long g;
+  int d;
+};
+template <bool PLANE>
+__device__ __forceinline__ RowMap space_rows(const TileArgs& a, long long tile) {
+  if constexpr (PLANE) {
+    if (a.B) {
+      const int z = fdiv((int)tile, a.mB), yb = (int)tile - z * a.B;
+      return {(long long)z * a.p.Ny * a.x.N + yb * a.x.N, a.B * a.x.N};
+    }
+  }
+  return {tile * a.rows * a.x.N, a.x.N};
+}
+
 // conj: the twiddles of the inverse direction
 template <bool PLANE>
 __device__ __forceinline__ TileLds tile_lds(const TileArgs& a, float2* lds, bool conj) {
@@ -72,7 +91,8 @@ __device__ __forceinline__ TileLds tile_lds(const TileArgs& a, float2* lds, bool
   }
   if constexpr (PLANE) {
     for (int i = threadIdx.x; i < a.y.N; i += blockDim.x) {
-      t.twy[i] = conj ? cconj(a.y.tw[i]) : a.y.tw[i];
+      const float2 w = a.y.tw[i * a.y.tws];
+      t.twy[i] = conj ? cconj(w) : w;
       const int f = freq_of(a.y, i);
       t.fy[i] = (u16)f;
       t.ys[f] = (u16)i;
@@ -190,7 +210,7 @@ __device__ __forceinline__ void x_first(const TileArgs& a, const TileLds& t, int
 
 // Last stage of the rows, to memory (PLANE: the rows are digit-reversed).
 template <int SM, int DT, bool PLANE, bool SEQ, bool INV>
-__device__ __forceinline__ void x_last(const TileArgs& a, const TileLds& t, int j, long long g0, int nrows) {
+__device__ __forceinline__ void x_last(const TileArgs& a, const TileLds& t, int j, RowMap m, int nrows) {
   const AxisT& x = a.x;
   const int i = x.nst - 1;
   with_stage<SEQ>(x, i, OS3D_SEQ_FN(rc, rb) {
@@ -208,7 +228,7 @@ __device__ __forceinline__ void x_last(const TileArgs& a, const TileLds& t, int 
 #pragma unroll
       for (int r = 0; r < R; ++r) v[r] = q[r];
       butterfly<SEQ, INV, false, R, RB>(x, i, t.twx, f, v, a.p.sgn);
-      tile_store<SM, DT, R, RB>(a.p, j, g0 + row * x.N + f, nf, v);
+      tile_store<SM, DT, R, RB>(a.p, j, m.g + row * m.d + f, nf, v);
     }
   });
 }
@@ -241,7 +261,7 @@ __device__ __forceinline__ void y_stage(const TileArgs& a, const TileLds& t, int
 
 // First stage of the columns, from memory.
 template <int LM, int DT, bool SEQ, bool INV>
-__device__ __forceinline__ void y_first(const TileArgs& a, const TileLds& t, int j, long long g0) {
+__device__ __forceinline__ void y_first(const TileArgs& a, const TileLds& t, int j, RowMap m) {
   const AxisT& y = a.y;
   const int S = y.S[0];
   with_stage<SEQ>(y, 0, OS3D_SEQ_FN(rc, rb) {
@@ -251,7 +271,7 @@ __device__ __forceinline__ void y_first(const TileArgs& a, const TileLds& t, int
       const int e = fdiv(id, a.mNx), col = id - e * a.x.N;
       const int b = fdiv(e, a.mP), row = (e - b * a.P) * a.A + b;
       float2 v[R];
-      tile_load<LM, DT, R>(a.p, j, g0 + row * a.x.N + col, (long long)S * a.x.N, v);
+      tile_load<LM, DT, R>(a.p, j, m.g + row * m.d + col, (long long)S * m.d, v);
       butterfly<SEQ, INV, false, R, RB>(y, 0, t.twy, 0, v, a.p.sgn);
       float2* q = t.buf + row * a.RS + t.xl[col];
       const int d = S * a.RS;
@@ -304,10 +324,10 @@ __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
           x_stage<SEQ, INV, false>(a, t, i);
           __syncthreads();
         }
-        x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, g0, nrows);
+        x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, {g0, a.x.N}, nrows);
       }
     } else if constexpr (!kXFirst) {
-      y_first<LM, DT, SEQ, INV>(a, t, j, g0);
+      y_first<LM, DT, SEQ, INV>(a, t, j, LM == LM_UIN ? space_rows<PLANE>(a, tile) : RowMap{g0, a.x.N});
       __syncthreads();
       for (int i = 1; i <= ly; ++i) {
         y_stage<SEQ, INV, false, false>(a, t, i, KeepInLds{});
@@ -317,7 +337,7 @@ __global__ __launch_bounds__(1024) void k_tile(TileArgs a) {
         x_stage<SEQ, INV, false>(a, t, i);
         __syncthreads();
       }
-      x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, g0, a.rows);
+      x_last<SM, DT, PLANE, SEQ, INV>(a, t, j, SM == SM_UOUT ? space_rows<PLANE>(a, tile) : RowMap{g0, a.x.N}, a.rows);
     } else {
       x_first<LM, DT, SEQ, INV>(a, t, j, g0, a.rows, KeepInLds{});
       __syncthreads();
@@ -356,7 +376,7 @@ __global__ __launch_bounds__(1024) void k_tile_phi(TileArgs a) {
     const long long tile = task - j * a.tiles, g0 = tile * n;
     const int nrows = PLANE ? a.rows : (int)min((long long)a.rows, a.nlines - tile * a.rows);
     if constexpr (PLANE) {
-      y_first<LM_C, OS3D_C64, false, true>(a, t, j, g0);
+      y_first<LM_C, OS3D_C64, false, true>(a, t, j, {g0, a.x.N});
       __syncthreads();
       for (int i = 1; i <= ly; ++i) {
         y_stage<false, true, false, false>(a, t, i, KeepInLds{});
@@ -437,7 +457,15 @@ static TileArgs tile_args(const os3d_bank* b, const PassArgs& p, bool plane, boo
   a.x = seq ? make_axis_seq(Nx, b->d.tw[2]) : make_axis(Nx, b->d.tw[2], true);
   a.y = seq ? make_axis_seq(Ny, b->d.tw[1]) : make_axis(Ny, b->d.tw[1]);
   a.RS = row_stride(a.x, a.pad);
-  if (plane) {
+  if (p.split) {  // a class of the rows of a plane
+    a.B = p.split;
+    a.mB = fdiv_mul((unsigned)a.B);
+    a.y = make_axis(Ny / a.B, b->d.tw[1]);
+    a.y.tws = a.B;
+    a.P = 1;
+    a.A = a.rows = Ny / a.B;
+    a.tiles = (long long)Nz * a.B;
+  } else if (plane) {
     // several planes of a small grid share a workgroup, as long as that
     // leaves four workgroups per CU
     a.A = Ny;
@@ -457,7 +485,7 @@ static TileArgs tile_args(const os3d_bank* b, const PassArgs& p, bool plane, boo
   a.mRL = fdiv_mul((unsigned)a.x.R[a.x.nst - 1]);
   a.mP = fdiv_mul((unsigned)a.P);
   a.mA = fdiv_mul((unsigned)a.A);
-  q.lds = tile_bytes(a.rows, a.RS, Nx, plane ? Ny : 0);
+  q.lds = tile_bytes(a.rows, a.RS, Nx, plane ? a.A : 0);
   a.mnf = fdiv_mul((unsigned)a.x.nb[a.x.nst - 1]);
   // a butterfly of ten values or so per thread; a workgroup that shares its CU takes up to 512 threads
   const int n = a.rows * Nx;

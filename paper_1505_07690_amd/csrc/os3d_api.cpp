@@ -191,12 +191,14 @@ os3d_status os3d_build_bank(const int64_t dims[3], const double* orients, int32_
   b->Npad = (b->n_unique + 15) / 16 * 16;
   // 256^3 volumes take the two-pass transform and its frequency tiles
   b->layout = (dims[0] == 256 && dims[1] == 256 && dims[2] == 256) ? 1 : 0;
-  if (b->layout == 0)
+  if (b->layout == 0) {
     b->plane = (dims[1] == dims[2] && (dims[2] == 64 || dims[2] == 128)) ? kPlaneFixed
                : plane_fits((int)dims[1], (int)dims[2])                  ? kPlaneTile
                                                                          : kPlaneNone;
+    if (b->plane == kPlaneNone) b->split = split_factor((int)dims[0], (int)dims[1], (int)dims[2]);
+  }
   if (const char* e = std::getenv("OS3D_THREE_PASS"))
-    if (e[0] == '1') b->layout = b->plane = 0;
+    if (e[0] == '1') b->layout = b->plane = b->split = 0;
   const BankLayout lay = layout(dims, b->n_unique, p->L);
   if (bank_bytes_given < lay.total) {
     delete b;

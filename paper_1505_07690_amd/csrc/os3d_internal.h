@@ -92,6 +92,7 @@ struct os3d_bank {
   int paired;
   int layout;                 // frequency storage order: 0 natural, 1 four-step tiles of 256^3
   int plane;                  // natural order: how the (y, x) planes are transformed (PlanePath)
+  int split;                  // kPlaneNone: factor of y that the z-line passes of the pairs take (0: none)
   int L;
   int Npad;
   int kblocks;                // K-blocks of the synthesis contraction
@@ -130,6 +131,7 @@ int launch_approx(const os3d_bank* b, const void* U, int dtype, const float* sca
 int launch_export_M(const os3d_bank* b, float* out, void* stream);
 size_t workspace_bytes(const os3d_bank* b);
 bool plane_fits(int Ny, int Nx);  // a (y, x) plane fits in LDS
+int split_factor(int Nz, int Ny, int Nx);  // factor of y that goes with the z lines of larger planes, or 0
 int profile_enable(int on);
 // Launch bracketing for the per-kernel timer: prof_start returns a token (or
 // null when timing is off) and leaves its events for the one launch that

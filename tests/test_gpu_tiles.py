@@ -37,8 +37,15 @@ SHAPES = {
     "y_4050": ((2, 4050, 3), "tetrahedron"),
     "x_4096": ((3, 2, 4096), "octahedron"),
     "three_factor_plane": ((6, 81, 162), "tetrahedron"),
-    "sum_shared_over_launches": ((12, 16, 18), 140),       # 140 stored rows: three launches
+    "sum_shared_over_launches": ((12, 16, 18), 140),       # 140 stored rows: two launches
     "sum_shared_one_launch": ((48, 20, 24), 30),
+    # planes past LDS: a factor of y goes with the z lines
+    "split_2_ragged_sum_shared": ((5, 162, 150), 30),      # 81 x 150 lines: not a multiple of 32
+    "split_4": ((3, 200, 250), "tetrahedron"),
+    "split_8_one_factor_z": ((2, 240, 405), "octahedron"),
+    "split_2_z_12_rows": ((36, 120, 180), "tetrahedron"),
+    "split_past_threads": ((243, 16, 1296), "tetrahedron"),  # z tile too large: three passes
+    "split_odd_y": ((3, 225, 100), "octahedron"),            # three passes
 }
 
 
