@@ -52,7 +52,9 @@ __device__ __forceinline__ int chunk_of(const TileArgs& a) {
   return a.xcd ? (int)(blockIdx.x & 7) * a.xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
 }
 
-__device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
+// conj: the twiddles of the inverse direction (conjugated here, before the
+// barrier: the first stage reads them where it joins two factors)
+__device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds, bool conj = false) {
   const AxisT& z = a.y;
   LineTile t;
   t.lw = a.lw;
@@ -64,7 +66,7 @@ __device__ __forceinline__ LineTile line_tile(const TileArgs& a, float2* lds) {
   t.fq = (u16*)(t.ts + (a.lb ? 1 << a.lw : 0));
   t.red = (float*)(t.fq + ((z.N + 1) & ~1));
   for (int i = threadIdx.x; i < z.N; i += blockDim.x) {
-    t.tw[i] = z.tw[i];
+    t.tw[i] = conj ? cconj(z.tw[i]) : z.tw[i];
     t.fq[i] = (u16)freq_of(z, i);
   }
   if (a.lb) {
@@ -484,7 +486,9 @@ __device__ __forceinline__ void line_seq_rest(const AxisT& z, const LineTile& t,
   }
 }
 
-// Conjugates the tile's twiddles (between barriers).
+// Conjugates the tile's twiddles: the caller has a barrier before it (earlier
+// stages read them) and one after it (so does the next stage, the first too
+// where it joins two factors).
 __device__ __forceinline__ void conj_twiddles(const AxisT& z, const LineTile& t) {
   for (int i = threadIdx.x; i < z.N; i += blockDim.x) t.tw[i].y = -t.tw[i].y;
 }
@@ -579,8 +583,7 @@ __global__ __launch_bounds__(1024) void k_line_y_seq(TileArgs a) {
   extern __shared__ float2 lds[];
   const PassArgs& p = a.p;
   const AxisT& y = a.y;
-  const LineTile t = line_tile(a, lds);
-  if (p.sgn > 0.f) conj_twiddles(y, t);
+  const LineTile t = line_tile(a, lds, p.sgn > 0.f);
   const int zp = blockIdx.x / a.chunks, x = ((blockIdx.x - zp * a.chunks) << a.lw) + t.c;
   const bool valid = x < p.Nx;
   const long long col = (long long)zp * p.Ny * p.Nx + (valid ? x : p.Nx - 1);

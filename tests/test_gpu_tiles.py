@@ -76,3 +76,24 @@ def test_tile_plans(name):
         assert rel(Ud, Uo) < bound
         rq = os3d.reconstruct(Uq, gb, scales=sc, dtype=fmt).cpu().numpy()
         assert rel(rq, O.reconstruct(Ud.astype(np.complex128), ob)) < TOL
+
+
+# Planes past LDS whose y lines begin with a stage of two factors: the 16-bit
+# forward transform takes z, y and x lines there.
+@pytest.mark.parametrize("shape", [(3, 150, 150), (3, 108, 200), (2, 243, 90), (2, 135, 160), (2, 90, 240)])
+def test_16_bit_scores_of_planes_past_lds(shape):
+    import torch
+    from paper_1505_07690_amd import os3d
+    n = inputs.platonic_orientations("octahedron")
+    p = O.WaveletParams(L=5, s_theta=inputs.s_theta_for(len(n)))
+    vols = [inputs.tubes(shape, 2, 1.2, 0.1, 0, s) for s in (71, 72)]
+    gb = os3d.Bank(shape, n, p)
+    ob = O.build_bank(shape, n, p)
+    f = torch.from_numpy(np.stack(vols)).cuda()
+    for fmt, bound in (("bf16", 4e-3), ("fp16", 5e-4)):
+        U, sc = os3d.forward(f, gb, dtype=fmt)
+        for i, vol in enumerate(vols):
+            Ua, sa = os3d.forward(f[i].contiguous(), gb, dtype=fmt)
+            assert torch.equal(Ua, U[i]) and torch.equal(sa, sc[i])
+            Ud = os3d.unpack16(Ua, sa, fmt).cpu().numpy()
+            assert rel(Ud, O.forward(vol.astype(np.float64), ob)) < bound
