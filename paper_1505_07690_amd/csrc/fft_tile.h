@@ -65,8 +65,7 @@ struct TileArgs {
   int xcd;             // chunks of an XCD (0: in the order of the workgroups)
   int groups;          // workgroups that share the pairs of a launch
   int two;             // the LDS holds two tiles: successive pairs alternate, one barrier a pair less
-  const float2* part;  // partial orientation sums of the groups 1.. (volumes)
-  int nparts;          // how many of them the inverse pass adds to its source
+  float2* part;        // the pairs' intermediates: group g > 0 sums into the first of its own
   int finish;          // the orientation sum goes on through the division and the inverse DFT
   // plane and row kernels
   int rows, P, A;      // rows = P A rows of x.N values per tile
@@ -384,10 +383,10 @@ inline AxisT make_axis_seq(int N, const float* tw) {
 
 // kernels_line.hip
 int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st);
-int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* parts, int groups, bool finish, hipStream_t st);
-int launch_zline_div(const os3d_bank* b, const PassArgs& p, const float2* parts, int nparts, hipStream_t st);
+int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* T, int groups, bool finish, hipStream_t st);
+int launch_zline_div(const os3d_bank* b, const PassArgs& p, float2* T, int groups, bool finish, hipStream_t st);
 int launch_yline(const os3d_bank* b, const PassArgs& p, bool seq, hipStream_t st);
-int zline_tiles(const os3d_bank* b, bool seq);     // workgroups of one volume's z lines
+int zline_tiles(const os3d_bank* b);               // workgroups of one volume's z lines (16-bit scores)
 int zline_acc_groups(const os3d_bank* b, int nb);  // partial sums of a launch over nb pairs
 // kernels_tile.hip: whole (y, x) planes, or x lines
 template <int LM, int SM>

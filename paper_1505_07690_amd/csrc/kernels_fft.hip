@@ -204,7 +204,10 @@ static int run_y(const os3d_bank* b, int kid, const PassArgs& a, bool seq, hipSt
 
 // Orientation pairs per launch: larger batches amortise the spectrum loads
 // and the orientation-sum read-modify-write and keep more workgroups in
-// flight; each pair costs one intermediate volume of workspace.
+// flight; each pair costs one intermediate volume of workspace.  96 x 80 x 64 with
+// 81 pairs takes 679 us a job in two launches (43 volumes) and 615 in one (83):
+// the pairs stay at 64, so that a job that fits next to others in a memory
+// budget goes on fitting.
 static int pair_batch(const os3d_bank* b) {
   int nb = kMaxBatch;
   if (const char* e = getenv("OS3D_PAIR_BATCH")) nb = atoi(e);
@@ -216,19 +219,16 @@ static int pair_batch(const os3d_bank* b) {
   return (b->n_unique + launches - 1) / launches;
 }
 
-// Partial orientation sums of a launch over nb pairs, the sum itself among them.
-static int sum_groups(const os3d_bank* b, int nb) {
-  return b->layout == kLayoutFour256 ? 1 : zline_acc_groups(b, nb);
-}
-
 size_t workspace_bytes(const os3d_bank* b) {
   const int nb = pair_batch(b);
-  const long long tiles = b->layout == kLayoutFour256 ? 1024 : std::max(zline_tiles(b, false), zline_tiles(b, true));
-  // F or X, one intermediate per pair of the batch, the partial orientation
-  // sums; processing via scores needs F and X, and at 256^3 two buffers per
-  // pair of a half batch
-  return (size_t)(2 + std::max(nb, 2) + sum_groups(b, nb) - 1) * b->V * sizeof(float2) +
-         (size_t)nb * tiles * sizeof(float) + 256;
+  // F or X, one intermediate per pair of the batch; processing via scores needs
+  // F and X, and at 256^3 two buffers per pair of a half batch.  The scale
+  // bounds of 16-bit scores (a float per pair and tile) have room of their own
+  // at 256^3; elsewhere they go into the volume that is X in processing: a
+  // tile holds Nz W values (W = 32 lines, fewer only where Nz > 32), so nb <= 64
+  // pairs take at most 8 V + 4 nb bytes.
+  const size_t bounds = b->layout == kLayoutFour256 ? (size_t)nb * 1024 * sizeof(float) : 0;
+  return (size_t)(2 + std::max(nb, 2)) * b->V * sizeof(float2) + bounds + 256;
 }
 
 // f transformed along x and y into F (the z lines follow in the spectral multiply).
@@ -255,10 +255,11 @@ static int planes_to_f(const os3d_bank* b, float2* X, float* f_out, hipStream_t 
 }
 
 // The weighted orientation sum of the nb intermediates T (transformed along x
-// and y) into X; the last launch of a volume goes on to X / max(M, eps) (or X
-// alone) transformed back along z.
-static int sum_pairs(const os3d_bank* b, const PassArgs& pairs, const float2* T, float2* X, float2* parts, int groups,
-                     bool first, bool last, bool divide_M, hipStream_t st) {
+// and y; overwritten) into X; the last launch of a volume goes on to X / max(M,
+// eps) (or X alone) transformed back along z.
+static int sum_pairs(const os3d_bank* b, const PassArgs& pairs, float2* T, float2* X, bool first, bool last,
+                     bool divide_M, hipStream_t st) {
+  const int groups = zline_acc_groups(b, pairs.nb);
   PassArgs z = pairs;
   z.src_c = T;
   z.src_stride = b->V;
@@ -269,11 +270,12 @@ static int sum_pairs(const os3d_bank* b, const PassArgs& pairs, const float2* T,
   z.divide = divide_M ? 1 : 0;
   const bool finish = last && groups == 1;
   int rc = timed(st, kProfRecLast, 0.0,
-                 [&]() -> int { return launch_zline_acc(b, z, parts, groups, finish, st); });
-  if (rc || !last || finish) return rc;
+                 [&]() -> int { return launch_zline_acc(b, z, T, groups, finish, st); });
+  if (rc || groups == 1) return rc;
   z.src_c = X;
   z.split = 0;
-  return timed(st, kProfInvFirst, 0.0, [&]() -> int { return launch_zline_div(b, z, parts, groups - 1, st); });
+  return timed(st, last ? kProfInvFirst : kProfRecLast, 0.0,
+               [&]() -> int { return launch_zline_div(b, z, T, groups, last, st); });
 }
 
 int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int dtype, float* scales, void* ws,
@@ -302,7 +304,7 @@ int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int d
       if ((rc = timed(st, kProfFwdFirst, 0.0, [&]() -> int { return launch_zline_mul(b, z, st); }))) return rc;
       if (quant) {
         rc = timed(st, kProfScales, 0.0, [&]() -> int {
-          launch_scales(partial, zline_tiles(b, true), z, dtype, sc, z.nb, st);
+          launch_scales(partial, zline_tiles(b), z, dtype, sc, z.nb, st);
           return OS3D_OK;
         });
         if (rc) return rc;
@@ -327,10 +329,8 @@ int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int d
 }
 
 int reduce_pair_batch(const os3d_bank* b, long long ws_bytes) {
-  // X, the partial sums and one intermediate volume per pair of a launch
-  const long long fit = ws_bytes / (b->V * (long long)sizeof(float2));
-  int nb = std::min<long long>(pair_batch(b), fit - 1);
-  while (nb >= 1 && nb + sum_groups(b, nb) > fit) --nb;
+  // X and one intermediate volume per pair of a launch
+  const int nb = (int)std::min<long long>(pair_batch(b), ws_bytes / (b->V * (long long)sizeof(float2)) - 1);
   if (nb < 1) return 0;
   const int launches = (b->n_unique + nb - 1) / nb;
   return (b->n_unique + launches - 1) / launches;
@@ -345,8 +345,6 @@ int launch_reduce(const os3d_bank* b, const void* U, int dtype, const float* sca
   const long long V = b->V;
   float2* X = (float2*)ws;
   float2* T = X + V;
-  float2* parts = T + (long long)nbmax * V;
-  const int groups = sum_groups(b, nbmax);
   const size_t ubytes = (dtype == OS3D_C64) ? 8 : 4;
   int rc;
   for (int bi = 0; bi < batch; ++bi) {
@@ -363,7 +361,7 @@ int launch_reduce(const os3d_bank* b, const void* U, int dtype, const float* sca
       x.src_c = T;
       x.src_stride = V;
       if (!b->plane && !x.split && (rc = run_y(b, kProfRecMid, x, false, st))) return rc;
-      if ((rc = sum_pairs(b, x, T, X, parts, groups, r0 == 0, r0 + nbmax >= b->n_unique, divide_M, st))) return rc;
+      if ((rc = sum_pairs(b, x, T, X, r0 == 0, r0 + nbmax >= b->n_unique, divide_M, st))) return rc;
     }
     if ((rc = planes_to_f(b, X, f_out + (long long)bi * V, st))) return rc;
   }
@@ -384,8 +382,6 @@ int launch_process(const os3d_bank* b, const float* f, int batch, int phi_kind, 
   float2* F = (float2*)ws;
   float2* X = F + V;
   float2* T = X + V;
-  float2* parts = T + (long long)nbp * V;
-  const int groups = sum_groups(b, nbp);
   int rc;
   for (int bi = 0; bi < batch; ++bi) {
     if ((rc = dft_planes_of_f(b, f + (long long)bi * V, F, false, st))) return rc;
@@ -411,7 +407,7 @@ int launch_process(const os3d_bank* b, const float* f, int batch, int phi_kind, 
       if (rc) return rc;
       z.sgn = -1.f;
       if (!b->plane && !z.split && (rc = run_y(b, kProfRecMid, z, false, st))) return rc;
-      if ((rc = sum_pairs(b, z, T, X, parts, groups, r0 == 0, r0 + nbp >= b->n_unique, true, st))) return rc;
+      if ((rc = sum_pairs(b, z, T, X, r0 == 0, r0 + nbp >= b->n_unique, true, st))) return rc;
     }
     if ((rc = planes_to_f(b, X, f_out + (long long)bi * V, st))) return rc;
   }

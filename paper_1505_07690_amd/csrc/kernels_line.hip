@@ -366,10 +366,17 @@ __device__ __forceinline__ void divide_inverse(const TileArgs& a, const LineTile
   });
 }
 
+// The first pair of group g.
+__device__ __forceinline__ int group_begin(const TileArgs& a, int g) {
+  return (int)((long long)a.p.nb * g / a.groups);
+}
+
 // DFT along z of every pair's intermediate, times its bank row, summed over
 // the workgroup's share of the pairs.  With few lines the pairs of a launch
-// are shared out to `groups` workgroups per tile (a volume of partial sums
-// each, added by k_line_div): 64^3 x 21 pairs has 128 tiles for 256 CUs.
+// are shared out to `groups` workgroups per tile: 64^3 x 21 pairs has 128 tiles
+// for 256 CUs.  Group 0 sums into X, the others into the intermediate of their
+// first pair, at the lines that the workgroup itself has read (k_line_div adds
+// them up), so a shared sum takes no workspace of its own.
 template <int RL, bool SPLIT>
 __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
   extern __shared__ float2 lds[];
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
 #pragma unroll
   for (int r = 0; r < RL; ++r) acc[r] = make_float2(0.f, 0.f);
   const int g = blockIdx.y;
-  const int j0 = (int)((long long)p.nb * g / a.groups), j1 = (int)((long long)p.nb * (g + 1) / a.groups);
+  const int j0 = group_begin(a, g), j1 = group_begin(a, g + 1);
   for (int j = j0; j < j1; ++j) {
     const float* row = p.psi + (long long)p.rows[j] * p.V + col;
     const float2* T = p.src_c + (long long)j * p.src_stride + col;
@@ -402,8 +409,8 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
       acc[r] = make_float2(acc[r].x + ps[r] * v[r].x, acc[r].y + ps[r] * v[r].y);
     });
   }
-  float2* X = (g == 0 ? p.dst_c : const_cast<float2*>(a.part) + (long long)(g - 1) * p.V) + col;
-  if (p.accumulate) each_freq<RL>(z, t, a.dn, [&](int r, long long o) { acc[r] = cadd(X[o], acc[r]); });
+  float2* X = (g == 0 ? p.dst_c : a.part + (long long)j0 * p.V) + col;
+  if (p.accumulate && g == 0) each_freq<RL>(z, t, a.dn, [&](int r, long long o) { acc[r] = cadd(X[o], acc[r]); });
   if (a.finish) {
     divide_inverse(a, t, acc, col, valid);
   } else if (valid && has_last<RL>(z, t)) {
@@ -411,7 +418,7 @@ __global__ __launch_bounds__(1024) void k_line_acc(TileArgs a) {
   }
 }
 
-// The partial orientation sums added up, divided by M, inverse DFT along z.
+// The groups' orientation sums added up into X; finish: divided by M, inverse DFT along z.
 template <int RL>
 __global__ __launch_bounds__(1024) void k_line_div(TileArgs a) {
   extern __shared__ float2 lds[];
@@ -423,11 +430,15 @@ __global__ __launch_bounds__(1024) void k_line_div(TileArgs a) {
 #pragma unroll
   for (int r = 0; r < RL; ++r) x[r] = make_float2(0.f, 0.f);
   each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { x[r] = p.src_c[o + col]; });
-  for (int g = 0; g < a.nparts; ++g) {
-    const float2* X = a.part + (long long)g * p.V + col;
+  for (int g = 1; g < a.groups; ++g) {
+    const float2* X = a.part + (long long)group_begin(a, g) * p.V + col;
     each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { x[r] = cadd(x[r], X[o]); });
   }
-  divide_inverse(a, t, x, col, valid);
+  if (a.finish) {
+    divide_inverse(a, t, x, col, valid);
+  } else if (valid && has_last<RL>(a.y, t)) {
+    each_freq<RL>(a.y, t, a.dn, [&](int r, long long o) { p.dst_c[o + col] = x[r]; });
+  }
 }
 
 // DFT of the y lines of every pair's volume, in place or from src to dst (one
@@ -723,14 +734,13 @@ static TileArgs zline_args(const os3d_bank* b, const PassArgs& p, LinePlan& q, b
   return a;
 }
 
-int zline_tiles(const os3d_bank* b, bool seq) {
+int zline_tiles(const os3d_bank* b) {
   LinePlan q;
-  return zline_args(b, PassArgs{}, q, seq).chunks;
+  return zline_args(b, PassArgs{}, q, true).chunks;
 }
 
 // With fewer tiles than fill the chip the pairs of a launch are shared out, at
-// least three to a workgroup (each share costs a volume of partial sums and
-// its read).
+// least three to a workgroup (each share costs a volume written and read).
 int zline_acc_groups(const os3d_bank* b, int nb) {
   LinePlan q;
   PassArgs p = {};
@@ -762,11 +772,11 @@ int launch_zline_mul(const os3d_bank* b, const PassArgs& p, hipStream_t st) {
   return check_line("k_line_mul");
 }
 
-int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* parts, int groups, bool finish, hipStream_t st) {
+int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* T, int groups, bool finish, hipStream_t st) {
   LinePlan q;
   TileArgs a = zline_args(b, p, q);
   a.groups = groups;
-  a.part = parts;
+  a.part = T;
   a.finish = finish ? 1 : 0;
   a.xcd = xcd_share(a);
   const dim3 grid((unsigned)(8 * a.xcd), (unsigned)a.groups);
@@ -777,11 +787,12 @@ int launch_zline_acc(const os3d_bank* b, const PassArgs& p, float2* parts, int g
   return check_line("k_line_acc");
 }
 
-int launch_zline_div(const os3d_bank* b, const PassArgs& p, const float2* parts, int nparts, hipStream_t st) {
+int launch_zline_div(const os3d_bank* b, const PassArgs& p, float2* T, int groups, bool finish, hipStream_t st) {
   LinePlan q;
   TileArgs a = zline_args(b, p, q);
-  a.part = parts;
-  a.nparts = nparts;
+  a.groups = groups;
+  a.part = T;
+  a.finish = finish ? 1 : 0;
   const dim3 grid((unsigned)a.chunks);
   with_radix(a.y.R[a.y.nst - 1], [&](auto rc) { launch_line(k_line_div<decltype(rc)::value>, grid, q, a, st); });
   return check_line("k_line_div");

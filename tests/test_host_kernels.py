@@ -75,3 +75,27 @@ def test_y_lines_of_16_bit_scores(driver, ny):
     # one order of the sums however the work is divided: the same stored words
     for name in ("forward_bf16", "forward_fp16"):
         assert lines[name] == planes[name]
+
+
+def intermediates(rows, cap=64):
+    """Pairs per launch: the fewest launches of at most `cap` pairs, evenly filled."""
+    launches = -(-rows // cap)
+    return -(-rows // launches)
+
+
+# (shape, rows, paired, route, split, batch, OS3D_PAIR_BATCH): pair sums shared
+# by several workgroups, in one launch and in several, on every route
+SHARED_SUMS = [((6, 5, 9), 140, False, PLANES, 0, 2, None),
+               ((8, 9, 5), 81, False, LINES, 0, 1, None),
+               ((5, 12, 15), 12, True, LINES, 2, 2, None),
+               ((9, 16, 10), 12, True, LINES, 4, 1, 7),
+               ((16, 6, 10), 21, True, PLANES, 0, 2, 9),
+               ((40, 3, 4), 12, False, LINES, 0, 1, None),
+               ((2, 4, 3), 64, False, PLANES, 0, 2, None)]  # the bounds of many pairs on the least grid
+
+
+@pytest.mark.parametrize("shape,rows,paired,route,split,batch,pairs", SHARED_SUMS)
+def test_workspace_holds_the_pairs_and_two_volumes(driver, shape, rows, paired, route, split, batch, pairs):
+    got = run(driver, shape, rows, paired, route, split, batch, pairs)
+    v = shape[0] * shape[1] * shape[2]
+    assert got["workspace"] <= (2 + max(2, intermediates(rows, pairs or 64))) * 8 * v + 256
