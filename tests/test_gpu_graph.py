@@ -51,3 +51,11 @@ def test_graph_replays_equal_eager(shape, level, L, dtype):
         torch.cuda.synchronize()
         assert torch.equal(got, rec), k
         assert np.isfinite(junk.item())
+
+
+@pytest.mark.parametrize("shape,dtype", [((4, 200, 250), "c64"), ((4, 200, 250), "bf16"), ((3, 225, 100), "c64"),
+                                         ((48, 40, 32), "c64")],
+                         ids=["split_c64", "split_bf16", "three_pass_c64", "plane_shared_sum_c64"])
+def test_graph_replays_of_line_and_tile_kernels(shape, dtype):
+    """Planes larger than LDS (split passes, y lines) and a sum shared by several workgroups."""
+    test_graph_replays_equal_eager(shape, 1, 8, dtype)

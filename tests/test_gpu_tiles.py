@@ -97,3 +97,40 @@ def test_16_bit_scores_of_planes_past_lds(shape):
             assert torch.equal(Ua, U[i]) and torch.equal(sa, sc[i])
             Ud = os3d.unpack16(Ua, sa, fmt).cpu().numpy()
             assert rel(Ud, O.forward(vol.astype(np.float64), ob)) < bound
+
+
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_soft_threshold_of_tile_plans(name):
+    """A Phi that commutes with no pass of the transform, on every plan."""
+    import torch
+    from paper_1505_07690_amd import os3d
+    shape, kind = SHAPES[name]
+    n = _random_orients(kind, 78) if isinstance(kind, int) else inputs.platonic_orientations(kind)
+    p = O.WaveletParams(L=5, s_theta=inputs.s_theta_for(len(n)))
+    vol = inputs.tubes(shape, 2, 1.2, 0.1, 0, 62)
+    ob = O.build_bank(shape, n, p)
+    got = os3d.process(torch.from_numpy(vol).cuda(), os3d.Bank(shape, n, p), "soft_threshold", 1.5).cpu().numpy()
+    assert rel(got, O.process(vol.astype(np.float64), ob, "soft_threshold", 1.5)) < TOL
+
+
+@pytest.mark.parametrize("name", ["sum_shared_over_launches", "sum_shared_one_launch", "split_2_ragged_sum_shared",
+                                  "split_odd_y", "three_factor_plane"])
+def test_batches_of_tile_plans(name):
+    """A batch of two equals its volumes run alone (the sums of one volume are reused by the next)."""
+    import torch
+    from paper_1505_07690_amd import os3d
+    shape, kind = SHAPES[name]
+    n = _random_orients(kind, 79) if isinstance(kind, int) else inputs.platonic_orientations(kind)
+    gb = os3d.Bank(shape, n, O.WaveletParams(L=5, s_theta=inputs.s_theta_for(len(n))))
+    f = torch.from_numpy(np.stack([inputs.tubes(shape, 2, 1.2, 0.1, 0, s) for s in (63, 64)])).cuda()
+    one = [f[i].contiguous() for i in range(2)]
+    gp = os3d.process(f, gb, "soft_threshold", 1.5)
+    for i in range(2):
+        assert torch.equal(gp[i], os3d.process(one[i], gb, "soft_threshold", 1.5))
+    for fmt in ("c64", "bf16"):
+        U, sc = os3d.forward(f, gb, dtype=fmt)
+        r = os3d.reconstruct(U, gb, scales=sc, dtype=fmt)
+        for i in range(2):
+            Ua, sa = os3d.forward(one[i], gb, dtype=fmt)
+            assert torch.equal(Ua, U[i]) and (sc is None or torch.equal(sa, sc[i]))
+            assert torch.equal(os3d.reconstruct(Ua, gb, scales=sa, dtype=fmt), r[i])

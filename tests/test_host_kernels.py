@@ -85,7 +85,7 @@ def intermediates(rows, cap=64):
 
 # (shape, rows, paired, route, split, batch, OS3D_PAIR_BATCH): pair sums shared
 # by several workgroups, in one launch and in several, on every route
-SHARED_SUMS = [((6, 5, 9), 140, False, PLANES, 0, 2, None),
+SHARED_SUMS = [((6, 5, 9), 70, False, PLANES, 0, 2, 24),
                ((8, 9, 5), 81, False, LINES, 0, 1, None),
                ((5, 12, 15), 12, True, LINES, 2, 2, None),
                ((9, 16, 10), 12, True, LINES, 4, 1, 7),
@@ -99,3 +99,13 @@ def test_workspace_holds_the_pairs_and_two_volumes(driver, shape, rows, paired, 
     got = run(driver, shape, rows, paired, route, split, batch, pairs)
     v = shape[0] * shape[1] * shape[2]
     assert got["workspace"] <= (2 + max(2, intermediates(rows, pairs or 64))) * 8 * v + 256
+
+
+# every kind of plan with a batch of two: one, two and three factors an axis,
+# several planes in a tile, ragged tiles, each split, unpaired sets
+@pytest.mark.parametrize("shape,rows,paired,route,split", [
+    ((9, 4, 5), 2, True, PLANES, 0), ((12, 30, 18), 2, False, PLANES, 0), ((4, 50, 12), 1, True, PLANES, 0),
+    ((20, 6, 36), 2, True, LINES, 0), ((18, 24, 10), 1, False, LINES, 0),
+    ((5, 18, 25), 2, True, LINES, 2), ((32, 12, 9), 1, False, LINES, 4), ((2, 48, 8), 2, True, LINES, 8)])
+def test_plans_in_both_orders(driver, shape, rows, paired, route, split):
+    run(driver, shape, rows, paired, route, split, batch=2)
