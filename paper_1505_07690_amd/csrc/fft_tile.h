@@ -20,12 +20,14 @@
 // Two factorisations.  The balanced one (radix_schedule) has the fewest
 // stages and twiddle-free composite butterflies.  The sequential one is for
 // the forward transform into 16-bit scores: there a last-bit difference of a
-// value near a rounding boundary changes the stored word, so its sums keep one
-// fixed order (the factors 16 .., 8 | 4 | 2, 5 .., 3 .. by decimation in
-// frequency in both directions, y before x on the way to space) however the
-// work is divided.  Two neighbouring factors share a stage when their product
-// is at most 16: the butterflies of both run in registers, with the second
-// one's twiddles in between.
+// value near a rounding boundary changes the stored word, and stored words are
+// kept from one version of the library to the next (a score written earlier
+// equals the one computed again).  So its sums keep one fixed order (the factors
+// 16 .., 8 | 4 | 2, 5 .., 3 .. by decimation in frequency in both directions, y
+// before x on the way to space) however the work is divided, and its products
+// the roundings that the words were first written with.  Two neighbouring
+// factors share a stage when their product is at most 16: the butterflies of
+// both run in registers, with the second one's twiddles in between.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -147,7 +149,10 @@ __host__ __device__ __forceinline__ void with_seq(int R, int RB, Fn f) {
 
 // Butterflies of the sequential schedule.  Left to itself the compiler picks
 // which product of a sum it fuses by the code around it, so here every sum
-// with two products names the fused one; hold() keeps a value rounded.
+// with two products names the fused one; hold() keeps a value rounded.  Which
+// product that is follows from no rule of the method: it is what the stored
+// words were first computed with (the lines of 64, 128 and 256 points by kernels
+// of their own, hence their second and third forms), each as accurate as the other.
 __device__ __forceinline__ void hold(float2& v) { asm("" : "+v"(v.x), "+v"(v.y)); }
 
 __device__ __forceinline__ float2 seq_mul(float2 a, float2 b) {

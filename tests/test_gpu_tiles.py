@@ -5,6 +5,10 @@ sums shared by several workgroups over several launches.  FP32 paths: relative
 L2 error <= 1e-5 (the bound of every FP32 path); 16-bit scores: the storage
 bound, and the reconstruction of the dequantised scores to 1e-5 (complex64
 intermediates)."""
+import hashlib
+import json
+import os
+
 import numpy as np
 import pytest
 
@@ -134,3 +138,26 @@ def test_batches_of_tile_plans(name):
             Ua, sa = os3d.forward(one[i], gb, dtype=fmt)
             assert torch.equal(Ua, U[i]) and (sc is None or torch.equal(sa, sc[i]))
             assert torch.equal(os3d.reconstruct(Ua, gb, scales=sa, dtype=fmt), r[i])
+
+
+# Stored 16-bit scores are the same words from one version of the library to
+# the next (they are files and baselines of its users): SHA-256 prefixes of the
+# words and scales, bf16 and fp16, from the library before its line and tile
+# kernels.  One grid per route and per kind of butterfly.
+with open(os.path.join(os.path.dirname(__file__), "golden", "score_words.json")) as _f:
+    WORDS = json.load(_f)
+
+
+@pytest.mark.parametrize("name", sorted(WORDS))
+def test_stored_words(name):
+    import torch
+    from paper_1505_07690_amd import os3d
+    shape = tuple(int(x) for x in name.split("x"))
+    n = inputs.platonic_orientations("octahedron") if np.prod(shape) > 2e5 else inputs.icosahedral_orientations(0)
+    gb = os3d.Bank(shape, n, os3d.make_params(L=5, s_theta=inputs.s_theta_for(len(n))))
+    f = torch.from_numpy(inputs.tubes(shape, 3, 1.3, 0.1, 0, 90)).cuda()
+    got = []
+    for fmt in ("bf16", "fp16"):
+        U, sc = os3d.forward(f, gb, dtype=fmt)
+        got.append(hashlib.sha256(U.cpu().numpy().tobytes() + sc.cpu().numpy().tobytes()).hexdigest()[:16])
+    assert got == WORDS[name]
