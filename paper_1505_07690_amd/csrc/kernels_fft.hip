@@ -313,10 +313,10 @@ int launch_forward(const os3d_bank* b, const float* f, int batch, void* U, int d
       z.src_stride = V;
       if (!b->plane && !z.split && (rc = run_y(b, kProfFwdMid, z, quant, st))) return rc;
       // the pass before wrote T in ascending order: its last pairs are still in
-      // the last-level cache (256 MB), so this one begins with them.  96 x 80 x 64
-      // x 162, forward + reconstruction: 654 -> 611 us; 160 x 128 x 128 x 42: 672
-      // -> 656.  With a pass over y between them reversing any of the passes gave
-      // nothing or lost 2 %.
+      // the last-level cache (256 MB), so this one begins with them.  Forward +
+      // reconstruction, oldest and newest first: 160 x 128 x 128 x 42 772 and 733 us,
+      // 128^3 x 42 641 and 600, 96 x 80 x 64 x 162 690 and 679.  With a pass over y
+      // between them reversing any of the passes gave nothing or lost 2 %.
       z.newest_first = b->plane || z.split ? 1 : 0;
       z.Uout = (char*)U + (size_t)bi * b->n_orients * V * ubytes;
       z.dtype = dtype;

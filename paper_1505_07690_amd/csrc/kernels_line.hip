@@ -15,9 +15,10 @@
 // (a tile is W lines of each of the B rows ka + kb A) and the plane pass
 // transforms the A rows of one class along y and x in LDS (kernels_tile.hip), so
 // the intermediate goes through memory once, not twice, for one more stage
-// in LDS.  Forward + reconstruction of 180 x 240 x 216 x 42 (B = 4): 4.73 -> 3.65
-// ms, 64 x 320 x 320 (B = 8): 3.27 -> 2.59 ms.  The forward into 16-bit scores
-// keeps three passes: its order of sums is fixed.
+// in LDS.  Forward + reconstruction with 42 orientations, in three passes and
+// split: 180 x 240 x 216 (B = 4) 4.58 and 3.52 ms, 64 x 320 x 320 (B = 8) 3.19 and
+// 2.42 ms.  The forward into 16-bit scores keeps three passes: its order of sums
+// is fixed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,8 +47,9 @@ struct LineTile {
 // to each, so that the cache lines that two chunks share (runs start anywhere in
 // a line of 128 bytes when Nx is no multiple of 16, and 16 bank entries are half a
 // line) are fetched by one XCD and their stores merge there.  Forward +
-// reconstruction of 256 x 192 x 192 x 42: 3.73 -> 3.56 ms, 64 x 320 x 320: 2.59 ->
-// 2.48 ms; processing of 120 x 100 x 90: 306 -> 295 us; 128^3: unchanged.
+// reconstruction with 42 orientations, chunks in turn and in runs: 256 x 192 x 192
+// 3.63 and 3.46 ms, 64 x 320 x 320 2.52 and 2.42 ms, 128^3 601 and 600 us;
+// processing of 120 x 100 x 90 309 and 296 us.
 __device__ __forceinline__ int chunk_of(const TileArgs& a) {
   return a.xcd ? (int)(blockIdx.x & 7) * a.xcd + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
 }
@@ -94,7 +96,8 @@ __device__ __forceinline__ bool line_of(const TileArgs& a, const LineTile& t, lo
 // ended before the barrier of the pair in between, or this one after a barrier.
 // Two tiles let a wave go on to the next pair while others still transform
 // this one (a stage of N / R butterflies leaves waves idle where the factors
-// differ).
+// differ): 96 x 80 x 64 x 162, forward + reconstruction, with one tile 688 us, with
+// two 679; processing of 120 x 100 x 90 x 42 301 and 296; 128^3 x 42 605 and 600.
 __device__ __forceinline__ void next_tile(const TileArgs& a, const LineTile& t0, LineTile& t, int i) {
   if (a.two) {
     t.buf = t0.buf + (i & 1) * (a.y.N << a.lw);
@@ -646,8 +649,9 @@ static int check_line(const char* what) {
 struct LinePlan {
   int lw, threads, two;
   size_t lds;
-  // workgroups that keep the chip busy: eight waves per CU (64^3 x 21 pairs: 95
-  // us a job, 97 with thirty-two; 96 x 80 x 64 x 81: 708 and 724)
+  // workgroups that keep the chip busy: eight waves per CU (forward +
+  // reconstruction with them and with thirty-two: 64^3 x 42 96 and 99.5 us, 128^3 x
+  // 42 600 and 621, 96 x 80 x 64 x 162 679 and 693)
   long long fill() const { return 256LL * 512 / threads; }
 };
 
@@ -661,8 +665,8 @@ static void launch_line(K kernel, dim3 grid, const LinePlan& q, const TileArgs& 
 // (up to 64 KB of tile, two workgroups per CU), at least runs of 16 values
 // where 1024 threads allow; down to runs of 32 values while the grid is smaller
 // than two workgroups per CU.  Shorter runs cost more than the idle CUs they
-// fill: at 180 x 240 x 216 (21 pairs) runs of 128 bytes instead of 256 take a
-// job from 4.72 to 5.25 ms, at 64^3 from 95 to 103 us.
+// fill: down to runs of 16 values forward + reconstruction of 64^3 x 42 takes 98.5
+// us instead of 96, processing of 96 x 80 x 64 x 162 477 instead of 455.
 static LinePlan line_plan(const AxisT& z, long long lines) {
   int rmin = 16;
   for (int i = 0; i < z.nst; ++i) rmin = std::min(rmin, z.R[i]);
@@ -682,9 +686,10 @@ static LinePlan line_plan(const AxisT& z, long long lines) {
 }
 
 // Split passes (p.split = B): tiles of B classes x W lines, W = 32, or 16 where
-// the LDS or 1024 threads don't hold that (100 x 180 x 180, B = 2: 1.31 ms a job
-// with 32, 1.47 with 16).  Runs of 8 lose what the pass over y costs: 256 x 192 x
-// 192 takes 4.4 ms with them, 4.2 in three passes and 3.7 with runs of 16.
+// the LDS or 1024 threads don't hold that (100 x 180 x 180 x 42, B = 2, forward +
+// reconstruction: 1.29 ms with 32, 1.43 with 16).  Runs of 8 lose what the pass
+// over y costs: 256 x 192 x 192 x 42 takes 4.03 ms with them, 4.01 in three passes
+// and 3.48 with runs of 16.
 static bool split_plan(const AxisT& z, int B, LinePlan& q, int& lb) {
   int rmin = 16;
   for (int i = 0; i < z.nst; ++i) rmin = std::min(rmin, z.R[i]);
@@ -702,9 +707,11 @@ static bool split_plan(const AxisT& z, int B, LinePlan& q, int& lb) {
   return false;
 }
 
-// The smallest B = 2, 4, 8 that leaves planes of Ny / B rows in LDS (a larger
-// one only widens the z-line tiles: 100 x 180 x 180 takes 1.43 ms a job with B = 4,
-// 1.82 with 8).  None: the pairs take three passes (z lines, y lines, x lines).
+// The smallest B = 2, 4, 8 that leaves planes of Ny / B rows in LDS.  The next
+// larger one trades wider z-line tiles for smaller planes, within a few percent
+// (forward + reconstruction with 42 orientations: 100 x 180 x 180 1.27 ms with B = 2
+// and 1.25 with 4, 100 x 160 x 180 1.11 and 1.08, 64 x 192 x 192 900 us with B = 4 and
+// 894 with 8).  None: the pairs take three passes (z lines, y lines, x lines).
 int split_factor(int Nz, int Ny, int Nx) {
   for (int B = 2; B <= 8; B *= 2) {
     LinePlan q;
