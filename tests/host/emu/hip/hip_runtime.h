@@ -4,8 +4,8 @@
 //
 // Between two barriers each wave runs to the end before the next one starts,
 // in ascending or (emu::reversed) descending order of workgroups, waves and
-// lanes.  Two kernels' results that differ between the two orders read memory
-// or LDS without the barrier that would order them.  LDS holds NaN before a
+// lanes.  A kernel whose results differ between the two orders reads memory or
+// LDS without the barrier that would order it after the write.  LDS holds NaN before a
 // workgroup starts and guard words after the launch's LDS bytes.
 #pragma once
 #include <ucontext.h>
